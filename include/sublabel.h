@@ -128,7 +128,9 @@ typedef struct {
   double best_primal, best_dual;
 } sl_report;
 
-/* Bytes of device workspace sl_create needs for this problem (no device work). */
+/* Bytes of device workspace sl_create needs for this problem (no device work). The last part
+ * holds the tile rims of the on-chip iteration (problems that fit the chip): a workspace
+ * without it is accepted too and runs every iteration as a launch of its own. */
 sl_status sl_workspace_size(const sl_problem_desc *desc, size_t *bytes);
 
 /* Validate desc, carve the caller's workspace (>= sl_workspace_size bytes, 256-byte
@@ -358,7 +360,8 @@ void sl_destroy(sl_problem p);
  * workspace taken from a fixed device array of the library instead of a caller's buffer.
  * That array holds SL_STATIC_WORKSPACE_BYTES per GPU; it is reserved on every GPU the
  * library's code is loaded on and held until the process ends. Problems whose
- * sl_workspace_size exceeds it return SL_ERR_UNSUPPORTED before any device work.
+ * sl_workspace_size (less the tile rims) exceeds it return SL_ERR_UNSUPPORTED before any
+ * device work.
  * The call makes no hipMalloc, hipFree, hipHostMalloc or other allocating call, and no
  * handle outlives it: the monitor's sums are copied into host memory of the call itself.
  * Every call on one GPU shares that GPU's array and re-initialises the state in it, so

@@ -10,7 +10,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libsublabel.so")
-SOURCES = ["capi.hip", "pdhg_iter.hip", "aux.hip", "adjoint.hip", "steps.hip", "stereo.hip", "temporal.hip"]
+SOURCES = ["capi.hip", "pdhg_iter.hip", "aux.hip", "adjoint.hip", "steps.hip", "stereo.hip", "temporal.hip",
+           "resident.hip", "resident_trunc.hip", "resident_quad.hip", "resident_sampled.hip"]
 ARCH = os.environ.get("SUBLABEL_OFFLOAD_ARCH", "gfx950")
 
 HIPCC_FLAGS = [
@@ -31,7 +32,7 @@ def _hipcc() -> str:
     return "hipcc"
 
 
-def build(verbose: bool = False, jobs: int = 4) -> str:
+def build(verbose: bool = False, jobs: int = 8) -> str:
     objdir = os.path.join(PKG, "_build")
     os.makedirs(objdir, exist_ok=True)
     hipcc = _hipcc()

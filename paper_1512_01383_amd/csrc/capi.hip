@@ -74,16 +74,26 @@ struct Trace {
   }
 };
 
+// kernel variant of a data-term kind (periodic pieces are quadratic pieces with a per-interval
+// centre, selected by IterArgs::per)
+int piece_of(sl_rho_kind rho) {
+  return rho == SL_RHO_TRUNC_QUAD ? SLI_TRUNC : rho == SL_RHO_SAMPLED ? SLI_SAMPLED : SLI_QUAD;
+}
+
 struct Layout {
   long long N, ps;
   size_t off_u, off_s, off_v, off_z, off_p, off_qd, off_fn, off_forig, off_w, off_cost, off_tau,
       off_taud, off_sinfo, off_sinfod;
   size_t off_monu, off_monb, off_part1, off_part2, off_fin, off_flag, total;
   size_t off_ysave, off_rpart, off_rfin;  // step control: duals before an iteration, residual sums
+  // rim words of the on-chip iteration, behind everything else: a workspace of `base` bytes
+  // serves too, without that path
+  size_t base, off_rim, rim;
   size_t state_lo, state_hi;  // contiguous range holding u, s, v, z, p, qd
 };
 
-Layout make_layout(const sl_problem_desc *d, int nb_mon) {
+// lone: a problem of its own (with room for the on-chip iteration), not a batch member
+Layout make_layout(const sl_problem_desc *d, int nb_mon, bool lone) {
   Layout L{};
   const int k = d->L - 1;
   L.N = (long long)d->H * d->W;
@@ -133,6 +143,9 @@ Layout make_layout(const sl_problem_desc *d, int nb_mon) {
     L.off_rpart = take((size_t)residual_blocks(A) * 32);
   }
   L.off_rfin = take(32);
+  L.base = o;
+  L.rim = lone ? resident_exchange_bytes(piece_of(d->rho), !sampled && d->samples, d->H, d->W, k) : 0;
+  L.off_rim = take(L.rim);
   L.total = o;
   return L;
 }
@@ -251,6 +264,10 @@ struct sl_problem_ {
   size_t pin_n = 0;
   // allocation-free problems stage those copies in this fixed host array instead
   bool no_alloc = false;
+  // on-chip iteration: whether this problem may use it, and the tag of the next rim word
+  bool resident = false;
+  int cus = 0;
+  unsigned rim_tag = 1;
   // two iterations per pass (temporal blocking): the caller's shadow state, 8k+1 planes
   char *band_ws = nullptr;
   double stage_fixed[16];
@@ -341,12 +358,6 @@ struct sl_problem_ {
 };
 
 namespace {
-
-// kernel variant of a data-term kind (periodic pieces are quadratic pieces with a per-interval
-// centre, selected by IterArgs::per)
-int piece_of(sl_rho_kind rho) {
-  return rho == SL_RHO_TRUNC_QUAD ? SLI_TRUNC : rho == SL_RHO_SAMPLED ? SLI_SAMPLED : SLI_QUAD;
-}
 
 // Iteration and monitor parameters from the problem description (labels and sample
 // positions from the copies kept in the handle; the caller's pointers are not kept).
@@ -501,14 +512,110 @@ sl_status band_quad(sl_problem_ *P) {
   return SL_OK;
 }
 
-// `iters` iterations; with a shadow workspace set (and band_ok) in groups of four by the
-// two-iteration kernel, the rest one at a time
-sl_status enqueue_iters(sl_problem_ *P, int iters, bool band_ok = true) {
-  if (band_ok && P->band_ws) {
+// Iterations from which a run is worth an on-chip launch: a cooperative launch costs about
+// 20 us more than a plain one (measured 21.0 against 2.2 us back to back), and an iteration
+// saves 3 us on the smallest problems and more on larger ones.
+constexpr int kResidentMin = 8;
+
+// `iters` iterations in one on-chip launch; *done is set if the problem and its stream allow
+// it (a stream that is being captured keeps the plain launches)
+sl_status resident_run(sl_problem_ *P, int iters, bool *done) {
+  *done = false;
+  ResidentPlan L;
+  if (!P->resident || iters < kResidentMin ||
+      !resident_plan(P->piece, P->add, P->A.H, P->A.W, P->A.k, kIterCfg[P->cfg][0], P->cus, &L) ||
+      (size_t)2 * L.blocks * P->A.k * (128 + 2 * L.th) * 8 > P->lay.rim)
+    return SL_OK;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(P->st, &cap) != hipSuccess) {
+    (void)hipGetLastError();
+    return SL_OK;
+  }
+  if (cap != hipStreamCaptureStatusNone) return SL_OK;
+  char *rim = P->ws + P->lay.off_rim;
+  if (P->rim_tag > 0xFFFFFFFFu - (unsigned)iters - 2u) {   // tags start over on cleared words
+    HIPCHK(launch_fill_zero(rim, P->lay.rim, P->st), "rim words");
+    P->rim_tag = 1;
+  }
+  const IterArgs &A = P->A;
+  ResidentArgs R;
+  memset(&R, 0, sizeof R);
+  R.u = P->ubuf(P->iu);
+  R.up = P->ubuf((P->iu + 2) % 3);
+  R.s = P->sbuf(P->is);
+  R.sp = P->sbuf(1 - P->is);
+  R.v = R.vo = P->ws + P->lay.off_v;
+  R.z = R.zo = P->ws + P->lay.off_z;
+  R.q = R.qo = (float *)(P->ws + P->lay.off_qd);
+  R.p = P->pbuf(P->ip);
+  const int iu = (P->iu + iters) % 3, is = (P->is + iters) % 2, ip = (P->ip + iters) % 2;
+  R.uo = P->ubuf(iu);
+  R.upo = P->ubuf((iu + 2) % 3);
+  R.so = P->sbuf(is);
+  R.spo = P->sbuf(1 - is);
+  R.po = P->pbuf(ip);
+  R.fn = (const float *)(P->ws + P->lay.off_fn);
+  R.wadd = (const float *)(P->ws + P->lay.off_w);
+  R.cost = (const float *)(P->ws + P->lay.off_cost);
+  R.tau = (const float4 *)(P->ws + P->lay.off_tau);
+  R.sinfo = (const unsigned *)(P->ws + P->lay.off_sinfo);
+  R.ex = (unsigned long long *)rim;
+  R.err = (unsigned *)(P->ws + P->lay.off_flag) + 1;
+  R.ps = A.ps;
+  R.H = A.H;
+  R.W = A.W;
+  R.k = A.k;
+  R.G = kIterCfg[P->cfg][0];
+  R.TH = L.th;
+  R.iters = iters;
+  R.tag = P->rim_tag;
+  R.sig_p = A.sig_p;
+  R.sig_q = A.sig_q;
+  R.tau_c = A.tau_c;
+  R.lam = A.lam;
+  R.a = A.a;
+  R.ia = A.ia;
+  R.nu = A.nu;
+  R.del = A.del;
+  R.per = A.per;
+  R.iper = A.iper;
+  R.aniso = A.aniso;
+  R.bf16 = P->bf16;
+  for (int j = 0; j <= A.k; j++) R.sidx[j] = A.sidx[j];
+  for (int i = 0; i < A.k; i++)
+    R.lab[i] = {A.gam[i], A.gam[i + 1], A.h[i], A.ih[i], A.sig[i], A.taus[i], A.ig0[i], A.ig1[i]};
+  const hipError_t e = launch_resident(P->piece, P->add, L, R, P->st);
+  if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
+    (void)hipGetLastError();
+    P->resident = false;   // fewer blocks fit here than the plan assumes: plain launches
+    return SL_OK;
+  }
+  if (e != hipSuccess) return hip_fail(e, "on-chip iterations launch");
+  P->rim_tag += (unsigned)iters + 1u;
+  P->iu = iu;
+  P->is = is;
+  P->ip = ip;
+  P->iters += iters;
+  *done = true;
+  return SL_OK;
+}
+
+// How enqueue_iters may run its iterations: one launch per iteration only; on-chip launches
+// too (bitwise the same iterates); or also, with a shadow workspace set, groups of four by
+// the two-iteration kernel (bitwise the iterates of one label group).
+enum RunBy { kOnePass, kSameBits, kAny };
+
+sl_status enqueue_iters(sl_problem_ *P, int iters, RunBy by = kAny) {
+  if (by == kAny && P->band_ws) {
     for (; iters >= 4; iters -= 4) {
       const sl_status s = band_quad(P);
       if (s != SL_OK) return s;
     }
+  }
+  if (by != kOnePass) {
+    bool done = false;
+    const sl_status s = resident_run(P, iters, &done);
+    if (s != SL_OK || done) return s;
   }
   for (int n = 0; n < iters; n++) {
     IterPtrs<float> Q = iter_ptrs_f(P);
@@ -1438,7 +1545,7 @@ sl_status sl_workspace_size(const sl_problem_desc *desc, size_t *bytes) {
   if (!bytes) return fail(SL_ERR_INVALID_ARG, "bytes is NULL");
   sl_status s = validate(desc);
   if (s != SL_OK) return s;
-  *bytes = make_layout(desc, monitor_blocks_max((long long)desc->H * desc->W)).total;
+  *bytes = make_layout(desc, monitor_blocks_max((long long)desc->H * desc->W), true).total;
   return SL_OK;
 }
 
@@ -1450,9 +1557,9 @@ static sl_status init_impl(sl_problem_ *P, const sl_problem_desc *desc, void *ws
   if (s != SL_OK) return s;
   if (!ws || ((uintptr_t)ws & 255)) return fail(SL_ERR_WORKSPACE, "workspace NULL or not 256-byte aligned");
   const int nb_mon = monitor_blocks_max((long long)desc->H * desc->W);
-  Layout lay = make_layout(desc, nb_mon);
-  if (bytes < lay.total)
-    return fail(SL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", bytes, lay.total);
+  Layout lay = make_layout(desc, nb_mon, true);
+  if (bytes < lay.base)
+    return fail(SL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", bytes, lay.base);
   int dev = -1;
   hipError_t e = hipGetDevice(&dev);
   if (e != hipSuccess) return hip_fail(e, "no HIP device");
@@ -1476,6 +1583,10 @@ static sl_status init_impl(sl_problem_ *P, const sl_problem_desc *desc, void *ws
   if (desc->tau) std::copy(desc->tau, desc->tau + desc->M, P->tau_in);
   fill_args(P);
   P->maxlds = maxlds;
+  int coop = 0;
+  HIPCHK(hipDeviceGetAttribute(&P->cus, hipDeviceAttributeMultiprocessorCount, dev), "device attribute");
+  HIPCHK(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev), "device attribute");
+  P->resident = coop && lay.rim > 0 && bytes >= lay.total;
   P->cfg = auto_cfg(P);
   if (P->cfg < 0) return fail(SL_ERR_UNSUPPORTED, "L = %d needs more LDS than a workgroup may use", desc->L);
   const long long N = lay.N;
@@ -1496,6 +1607,8 @@ static sl_status init_impl(sl_problem_ *P, const sl_problem_desc *desc, void *ws
   // zero state, data planes
   if ((e = launch_fill_zero(P->ws + lay.state_lo, lay.state_hi - lay.state_lo, P->st)) != hipSuccess)
     return hip_fail(e, "zero state");
+  if (P->resident && (e = launch_fill_zero(P->ws + lay.off_rim, lay.rim, P->st)) != hipSuccess)
+    return hip_fail(e, "rim words");
   if (P->piece != SLI_SAMPLED) {
     float fs = (float)P->shift, is = (float)(1.0 / P->scale);
     if ((e = launch_init_fn(desc->f, (float *)(P->ws + lay.off_fn), N, fs, is, P->st)) != hipSuccess)
@@ -1652,7 +1765,7 @@ sl_status sl_batch_workspace_size(const sl_problem_desc *descs, int32_t n, size_
   for (int i = 0; i < n; i++) {
     sl_status s = validate(&descs[i]);
     if (s != SL_OK) return fail(s, "instance %d: %s", i, g_err.c_str());
-    total += align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W)).total);
+    total += align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W), false).total);
     maxtiles.push_back(max_tiles(descs[i].H, descs[i].W));
   }
   *bytes = total + batch_table_bytes(maxtiles, n);
@@ -1685,7 +1798,7 @@ sl_status sl_batch_create(const sl_problem_desc *descs, int32_t n, void *ws, siz
   size_t off = 0;
   std::vector<int> maxtiles;
   for (int i = 0; i < n; i++) {
-    const size_t sz = align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W)).total);
+    const size_t sz = align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W), false).total);
     sl_problem q = nullptr;
     s = create_impl(&descs[i], base + off, sz, stream, &q);
     if (s != SL_OK) {
@@ -1868,10 +1981,10 @@ sl_status sl_autotune(sl_problem P, int32_t iters, const char *cache_path, int32
         if (!cfg_fits(P, c)) continue;
         P->cfg = c;
         if (P->is_batch && batch_rebuild_items(P) != SL_OK) continue;
-        sl_status s = P->is_batch ? batch_enqueue(P, 6) : enqueue_iters(P, 2, false);
+        sl_status s = P->is_batch ? batch_enqueue(P, 6) : enqueue_iters(P, 2, kOnePass);
         if (s != SL_OK) return s;
         HIPCHK(hipEventRecord(e0, P->st), "event record");
-        s = P->is_batch ? batch_enqueue(P, iters) : enqueue_iters(P, iters, false);
+        s = P->is_batch ? batch_enqueue(P, iters) : enqueue_iters(P, iters, kOnePass);
         if (s != SL_OK) return s;
         HIPCHK(hipEventRecord(e1, P->st), "event record");
         HIPCHK(hipEventSynchronize(e1), "event sync");
@@ -1940,7 +2053,7 @@ sl_status sl_unrolled_forward(sl_problem P, int32_t K, int32_t C, void *ws, size
       ck += np[g] * pl;
     }
     HIPCHK(hipMemcpyAsync(ck, P->pbuf(P->ip), 2 * k * pl, hipMemcpyDeviceToDevice, P->st), "checkpoint");
-    s = enqueue_iters(P, std::min(C, K - c * C), false);   // the replay's configuration
+    s = enqueue_iters(P, std::min(C, K - c * C), kSameBits);   // the replay's configuration
     if (s != SL_OK) return s;
   }
   P->uws = w;
@@ -2234,9 +2347,10 @@ sl_status sl_solve_static(const sl_problem_desc *desc, double rel_gap, int32_t m
                           float *u_dev, sl_report *report, void *hip_stream) {
   if (max_iters < 0 || !(rel_gap >= 0.0) || !isfinite(rel_gap))
     return fail(SL_ERR_INVALID_ARG, "bad rel_gap / max_iters");
-  size_t need = 0;
-  sl_status s = sl_workspace_size(desc, &need);
+  sl_status s = validate(desc);
   if (s != SL_OK) return s;
+  // (a problem that fits without the on-chip iteration's rim words runs without them)
+  const size_t need = make_layout(desc, monitor_blocks_max((long long)desc->H * desc->W), true).base;
   if (need > (size_t)SL_STATIC_WORKSPACE_BYTES)
     return fail(SL_ERR_UNSUPPORTED, "the problem needs %zu bytes of workspace; the allocation-free solve "
                 "has %zu", need, (size_t)SL_STATIC_WORKSPACE_BYTES);

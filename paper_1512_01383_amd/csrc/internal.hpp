@@ -110,6 +110,40 @@ struct BandPtrs {
 // QUAD and TRUNC pieces without additive values, FP32 storage
 hipError_t launch_pdhg_band(int piece, const BandPtrs &P, const IterArgs &A, hipStream_t st);
 
+// Many iterations per launch with the state on chip (resident.hpp). The state at iteration n
+// is read from u .. q and the state at n + iters written to uo .. qo, which may be the same
+// planes; ex holds two slots of rim words per tile, err is raised if a wait was given up.
+struct ResidentLabel {
+  float g0, g1, h, ih, sig, taus, ig0, ig1;
+};
+struct ResidentArgs {
+  const float *u, *up, *s, *sp, *q;
+  const void *v, *z, *p;
+  float *uo, *upo, *so, *spo, *qo;
+  void *vo, *zo, *po;
+  const float *fn, *wadd, *cost;
+  const float4 *tau;
+  const unsigned *sinfo;
+  unsigned long long *ex;
+  unsigned *err;
+  long long ps;
+  int H, W, k, G, TH, iters;
+  unsigned tag;           // of the state at n; tag + i names iteration n + i
+  float sig_p, sig_q, tau_c, lam, a, ia, nu, del, per, iper;
+  int aniso, bf16;
+  int sidx[SLI_MAXK + 1];
+  ResidentLabel lab[SLI_MAXK + 16];   // zeros past the last label
+};
+// How a problem is laid over the chip: labels and label groups per thread, tile rows, blocks.
+struct ResidentPlan {
+  int ch, lg, th, blocks, threads;
+  size_t lds;
+};
+// a plan for the problem with G label groups on `cus` compute units; false if it does not fit
+bool resident_plan(int piece, bool add, int H, int W, int k, int G, int cus, ResidentPlan *out);
+size_t resident_exchange_bytes(int piece, bool add, int H, int W, int k);   // 0 if no plan fits
+hipError_t launch_resident(int piece, bool add, const ResidentPlan &L, const ResidentArgs &R, hipStream_t st);
+
 // Double-precision problem parameters for the monitor (the certificate is evaluated for
 // the problem defined by the caller's double labels / coefficients and the FP32 data).
 struct MonArgs {

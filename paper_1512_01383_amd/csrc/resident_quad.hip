@@ -1,0 +1,6 @@
+// resident_quad.hip -- the on-chip iteration (resident.hpp) for quadratic pieces
+#include "resident.hpp"
+
+const void *resident_kernel_quad(bool add, int ch, int lg) {
+  return add ? resident::kernel_of<SLI_QUAD, true>(ch, lg) : resident::kernel_of<SLI_QUAD, false>(ch, lg);
+}

@@ -1,0 +1,4 @@
+// resident_sampled.hip -- the on-chip iteration (resident.hpp) for sampled costs
+#include "resident.hpp"
+
+const void *resident_kernel_sampled(bool, int ch, int lg) { return resident::kernel_of<SLI_SAMPLED, false>(ch, lg); }
