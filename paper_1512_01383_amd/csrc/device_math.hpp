@@ -166,34 +166,34 @@ __device__ __forceinline__ void proj_quad(float a, float ia, float c, float g0, 
   const float t = fminf(fmaxf(c + y * ia, g0), g1);
   const float dt = t - c;
   const float g = t * y - 0.5f * a * dt * dt;
-  if (w >= g) return;
   const float d0 = g0 - c, d1 = g1 - c;
   const float rho0 = 0.5f * a * d0 * d0, rho1 = 0.5f * a * d1 * d1;
   const float mul = (g0 * y - rho0 - w) * ig0;
   const float yl = y - mul * g0;
-  if (mul >= 0.f && yl <= a * d0) {
-    y = yl;
-    w = g0 * yl - rho0;
-    return;
-  }
   const float mur = (g1 * y - rho1 - w) * ig1;
   const float yr = y - mur * g1;
-  if (mur >= 0.f && yr >= a * d1) {
-    y = yr;
-    w = g1 * yr - rho1;
-    return;
+  // which part holds the point, by selects (the lanes of a wavefront stand in all of them);
+  // only the parabola's foot is worth a branch
+  const bool inside = w >= g;
+  const bool left = mul >= 0.f && yl <= a * d0, right = mur >= 0.f && yr >= a * d1;
+  const bool ray = !inside && (left || right), arc = !inside && !left && !right;
+  const float yn = left ? yl : yr;
+  const float wn = left ? g0 * yl - rho0 : g1 * yr - rho1;
+  y = ray ? yn : y;
+  w = ray ? wn : w;
+  if (arc) {
+    const float ac = a * c;
+    float Y = parabola_root(a, y + ac, w + 0.5f * ac * c);
+    Y = fminf(fmaxf(Y, a * g0), a * g1);
+    // one Newton step on the stationarity (yy - y) + (g(yy) - w) g'(yy) = 0 in the original
+    // coordinates removes the cancellation of the shift by a c
+    float yy = Y - ac;
+    const float gp = c + yy * ia, gv = yy * (c + 0.5f * yy * ia) - w;
+    const float den = 1.f + gp * gp + gv * ia;
+    if (den > 0.f) yy = fminf(fmaxf(yy - ((yy - y) + gv * gp) * frcp(den), a * d0), a * d1);
+    y = yy;
+    w = yy * (c + 0.5f * yy * ia);
   }
-  const float ac = a * c;
-  float Y = parabola_root(a, y + ac, w + 0.5f * ac * c);
-  Y = fminf(fmaxf(Y, a * g0), a * g1);
-  // one Newton step on the stationarity (yy - y) + (g(yy) - w) g'(yy) = 0 in the original
-  // coordinates removes the cancellation of the shift by a c
-  float yy = Y - ac;
-  const float gp = c + yy * ia, gv = yy * (c + 0.5f * yy * ia) - w;
-  const float den = 1.f + gp * gp + gv * ia;
-  if (den > 0.f) yy = fminf(fmaxf(yy - ((yy - y) + gv * gp) * frcp(den), a * d0), a * d1);
-  y = yy;
-  w = y * (c + 0.5f * y * ia);
 }
 
 // ---------------------------------------------------------------- piecewise-linear pieces
@@ -385,71 +385,72 @@ __device__ __forceinline__ void proj_tq_chain(float a, float c, float nu, float 
   const int nb = ml <= mr ? mr - ml + 1 : 0;
   const int nk = nb + 1;   // kinks
   // values at the two ends and at the first band sample, and the slopes of the two end
-  // kinks, once per call; the searches below then cost a few selects per halving
+  // kinks, once per call; the searches below then cost a few selects per halving. All
+  // selects, no branches: the lanes of a wavefront stand at different vertices, so a branch
+  // would run both sides under masks.
   const float rs0 = tq_sample(a, c, nu, g0, g1, hs, 0);
   const float rsN = tq_sample(a, c, nu, g0, g1, hs, SLI_NSUB - 1);
   const float rs1 = tq_sample(a, c, nu, g0, g1, hs, ml);
-  auto vt = [&](int v) { return v == 0 ? g0 : (v == nb + 1 ? g1 : g0 + hs * (float)(ml + v - 1)); };
-  auto vr = [&](int v) {
-    if (v == 0) return rs0;
-    if (v == nb + 1) return rsN;
-    if (v == 1) return rs1;
-    const float d = vt(v) - c;
-    return 0.5f * a * d * d;
+  const int mf = ml - 1;   // vertex v between the ends is sample mf + v
+  auto vt = [&](int v) {
+    float t = g0 + hs * (float)(mf + v);
+    t = v == nk ? g1 : t;
+    return v == 0 ? g0 : t;
   };
-  const float kb0 = (vr(1) - vr(0)) * frcp(vt(1) - vt(0));
-  const float kbN = (vr(nb + 1) - vr(nb)) * frcp(vt(nb + 1) - vt(nb));
+  auto vrt = [&](int v, float t) {   // value at vertex v, whose position is t
+    const float d = t - c;
+    float r = 0.5f * a * d * d;
+    r = v == 1 ? rs1 : r;
+    r = v == nk ? rsN : r;
+    return v == 0 ? rs0 : r;
+  };
+  const float t1 = vt(1), tb = vt(nb);
+  const float kb0 = (vrt(1, t1) - rs0) * frcp(t1 - g0);
+  const float kbN = (rsN - vrt(nb, tb)) * frcp(g1 - tb);
+  // slope of kink j, between vertices j and j + 1
   auto kb = [&](int j) {
-    if (j == 0) return kb0;
-    if (j == nb) return kbN;
-    return a * (vt(j + 1) - 0.5f * hs - c);
+    const float t = g0 + hs * (float)(mf + j + 1);
+    float b = a * (t - 0.5f * hs - c);
+    b = j == nb ? kbN : b;
+    return j == 0 ? kb0 : b;
   };
   const float y0 = y, w0 = w;
   // part under y0: the first kink at or right of it
   int lo = 0, hi = nk;
 #pragma unroll
-  for (int it = 0; it < 4; it++)
-    if (lo < hi) {
-      const int m = (lo + hi) >> 1;
-      if (y0 <= kb(m))
-        hi = m;
-      else
-        lo = m + 1;
-    }
-  if (w0 >= vt(lo) * y0 - vr(lo)) return;
+  for (int it = 0; it < 4; it++) {
+    const int m = (lo + hi) >> 1;
+    const bool open = lo < hi, left = y0 <= kb(m);
+    hi = open && left ? m : hi;
+    lo = open && !left ? m + 1 : lo;
+  }
+  const float tu = vt(lo);
+  if (w0 >= tu * y0 - vrt(lo, tu)) return;
   // region: the first kink whose cone lies right of the point
   lo = 0;
   hi = nk;
 #pragma unroll
-  for (int it = 0; it < 4; it++)
-    if (lo < hi) {
-      const int m = (lo + hi) >> 1;
-      const float b = kb(m), t = vt(m);
-      const float dy = y0 - b, dw = t * b - vr(m) - w0;
-      if (dw > 0.f ? dy < t * dw : dy < 0.f)
-        hi = m;
-      else
-        lo = m + 1;
-    }
-  int part = lo;   // strip of this part, unless the point sits in the cone of kink lo - 1
-  if (lo > 0) {
-    const int j = lo - 1;
-    const float b = kb(j), t = vt(j), t1 = vt(j + 1);
-    const float G = t * b - vr(j);
-    const float dy = y0 - b, dw = G - w0;
-    if (!(dw > 0.f ? dy > t1 * dw : dy > 0.f)) {
-      y = b;
-      w = G;
-      return;
-    }
+  for (int it = 0; it < 4; it++) {
+    const int m = (lo + hi) >> 1;
+    const float b = kb(m), t = vt(m);
+    const float dy = y0 - b, dw = t * b - vrt(m, t) - w0;
+    const bool open = lo < hi, left = dy < (dw > 0.f ? t * dw : 0.f);
+    hi = open && left ? m : hi;
+    lo = open && !left ? m + 1 : lo;
   }
-  const float t = vt(part), r = vr(part);
+  // strip of part lo, unless the point sits in the cone of kink lo - 1
+  const int part = lo;
+  const float t = vt(part), r = vrt(part, t);
+  const float bl = kb(part - 1), tl = vt(part - 1);
+  const float G = tl * bl - vrt(part - 1, tl);
+  const float dy = y0 - bl, dw = G - w0;
+  const bool cone = part > 0 && !(dy > (dw > 0.f ? t * dw : 0.f));
   const float mu = (t * y0 - r - w0) * frcp(1.f + t * t);
   float yf = y0 - mu * t;
-  if (part > 0) yf = fmaxf(yf, kb(part - 1));
-  if (part < nk) yf = fminf(yf, kb(part));
-  y = yf;
-  w = t * yf - r;
+  yf = part > 0 ? fmaxf(yf, bl) : yf;
+  yf = part < nk ? fminf(yf, kb(part)) : yf;
+  y = cone ? bl : yf;
+  w = cone ? G : t * yf - r;
 }
 
 // Constant piece nu on [g0, g1]: the conjugate is max(g0 y, g1 y) - nu with one kink at
