@@ -80,6 +80,24 @@ int piece_of(sl_rho_kind rho) {
   return rho == SL_RHO_TRUNC_QUAD ? SLI_TRUNC : rho == SL_RHO_SAMPLED ? SLI_SAMPLED : SLI_QUAD;
 }
 
+// the most label intervals of a truncated-quadratic problem that lie inside the band of one
+// pixel, whose width is 2 del: with room for the rounding of fc -+ del (|fc| is at most
+// max |gamma| + del where any interval lies inside)
+int band_most(const sl_problem_desc *d) {
+  if (d->rho != SL_RHO_TRUNC_QUAD) return 0;
+  const int k = d->L - 1;
+  const double scale = d->normalize_labels ? d->gamma[k] - d->gamma[0] : 1.0, shift = d->normalize_labels ? d->gamma[0] : 0.0;
+  const double del = sqrt(2.0 * d->nu / (d->a * scale * scale));
+  auto g = [&](int j) { return (d->gamma[j] - shift) / scale; };
+  const double room = 2.0 * del + 1e-6 * (std::max(fabs(g(0)), fabs(g(k))) + del);
+  int most = 0;
+  for (int i = 0, j = 0; i < k; i++) {
+    while (j < k && g(j + 1) - g(i) <= room) j++;
+    most = std::max(most, j - i);
+  }
+  return most;
+}
+
 struct Layout {
   long long N, ps;
   size_t off_u, off_s, off_v, off_z, off_p, off_qd, off_fn, off_forig, off_w, off_cost, off_tau,
@@ -144,7 +162,8 @@ Layout make_layout(const sl_problem_desc *d, int nb_mon, bool lone) {
   }
   L.off_rfin = take(32);
   L.base = o;
-  L.rim = lone ? resident_exchange_bytes(piece_of(d->rho), !sampled && d->samples, d->H, d->W, k) : 0;
+  L.rim = lone ? resident_exchange_bytes(piece_of(d->rho), !sampled && d->samples, d->H, d->W, k,
+                                         band_most(d)) : 0;
   L.off_rim = take(L.rim);
   L.total = o;
   return L;
@@ -268,6 +287,7 @@ struct sl_problem_ {
   bool resident = false;
   int cus = 0;
   unsigned rim_tag = 1;
+  int qmax = 0;
   // two iterations per pass (temporal blocking): the caller's shadow state, 8k+1 planes
   char *band_ws = nullptr;
   double stage_fixed[16];
@@ -523,8 +543,8 @@ sl_status resident_run(sl_problem_ *P, int iters, bool *done) {
   *done = false;
   ResidentPlan L;
   if (!P->resident || iters < kResidentMin ||
-      !resident_plan(P->piece, P->add, P->A.H, P->A.W, P->A.k, kIterCfg[P->cfg][0], P->cus, &L) ||
-      (size_t)2 * L.blocks * P->A.k * (128 + 2 * L.th) * 8 > P->lay.rim)
+      !resident_plan(P->piece, P->add, P->A.H, P->A.W, P->A.k, kIterCfg[P->cfg][0], P->qmax, P->cus, &L) ||
+      resident_rim_bytes(L, P->A.k) > P->lay.rim)
     return SL_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(P->st, &cap) != hipSuccess) {
@@ -581,6 +601,8 @@ sl_status resident_run(sl_problem_ *P, int iters, bool *done) {
   R.iper = A.iper;
   R.aniso = A.aniso;
   R.bf16 = P->bf16;
+  R.qmax = P->qmax;
+  R.slots = L.slots;
   for (int j = 0; j <= A.k; j++) R.sidx[j] = A.sidx[j];
   for (int i = 0; i < A.k; i++)
     R.lab[i] = {A.gam[i], A.gam[i + 1], A.h[i], A.ih[i], A.sig[i], A.taus[i], A.ig0[i], A.ig1[i]};
@@ -1586,6 +1608,7 @@ static sl_status init_impl(sl_problem_ *P, const sl_problem_desc *desc, void *ws
   int coop = 0;
   HIPCHK(hipDeviceGetAttribute(&P->cus, hipDeviceAttributeMultiprocessorCount, dev), "device attribute");
   HIPCHK(hipDeviceGetAttribute(&coop, hipDeviceAttributeCooperativeLaunch, dev), "device attribute");
+  P->qmax = band_most(desc);
   P->resident = coop && lay.rim > 0 && bytes >= lay.total;
   P->cfg = auto_cfg(P);
   if (P->cfg < 0) return fail(SL_ERR_UNSUPPORTED, "L = %d needs more LDS than a workgroup may use", desc->L);

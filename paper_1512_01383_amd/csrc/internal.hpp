@@ -131,17 +131,20 @@ struct ResidentArgs {
   unsigned tag;           // of the state at n; tag + i names iteration n + i
   float sig_p, sig_q, tau_c, lam, a, ia, nu, del, per, iper;
   int aniso, bf16;
+  int qmax, slots;        // most labels of a pixel inside the band; and listed: the straddling ones too
   int sidx[SLI_MAXK + 1];
   ResidentLabel lab[SLI_MAXK + 16];   // zeros past the last label
 };
-// How a problem is laid over the chip: labels and label groups per thread, tile rows, blocks.
+// How a problem is laid over the chip: labels, label groups and rows per thread, wavefronts on
+// top of each other in a tile, blocks.
 struct ResidentPlan {
-  int ch, lg, th, blocks, threads;
+  int ch, lg, rp, th, blocks, threads, slots;
   size_t lds;
 };
 // a plan for the problem with G label groups on `cus` compute units; false if it does not fit
-bool resident_plan(int piece, bool add, int H, int W, int k, int G, int cus, ResidentPlan *out);
-size_t resident_exchange_bytes(int piece, bool add, int H, int W, int k);   // 0 if no plan fits
+bool resident_plan(int piece, bool add, int H, int W, int k, int G, int qmax, int cus, ResidentPlan *out);
+size_t resident_rim_bytes(const ResidentPlan &L, int k);
+size_t resident_exchange_bytes(int piece, bool add, int H, int W, int k, int qmax);   // 0 if no plan fits
 hipError_t launch_resident(int piece, bool add, const ResidentPlan &L, const ResidentArgs &R, hipStream_t st);
 
 // Double-precision problem parameters for the monitor (the certificate is evaluated for

@@ -50,6 +50,16 @@ CASES = [
     ("add", 45, 130, 8, 0, "fp32", None),
     ("sampled", 40, 90, 4, 0, "fp32", None),
     ("sampled", 31, 64, 9, 1, "bf16", (1, 4, 64)),
+    # several rows per thread: two (a last tile of one row), three, twelve; two of several labels
+    ("quad", 521, 513, 2, 0, "fp32", None),
+    ("trunc", 700, 705, 2, 0, "bf16", None),
+    ("quad", 1531, 2039, 2, 0, "fp32", None),
+    ("phase", 500, 700, 6, 1, "fp32", None),
+    ("trunc", 530, 513, 4, 0, "fp32", None),
+    # long label chunks, whose rim words are waited for in turns
+    ("trunc", 353, 517, 10, 1, "fp32", None),
+    ("trunc", 490, 510, 9, 0, "bf16", None),
+    ("sampled", 260, 333, 9, 0, "fp32", (1, 4, 64)),
 ]
 
 
