@@ -18,6 +18,7 @@
 #include "device_math.hpp"
 #include "internal.hpp"
 #include "checks.hpp"
+#include "residuals.hpp"
 
 namespace {
 
@@ -561,6 +562,36 @@ __global__ __launch_bounds__(MB) void monitor_final(const double *part1, const d
   mon_final_body(part1, part2, nb, out, blockIdx.x);
 }
 
+// A check of one problem: the certificate's pixel terms and the residuals of the interval's
+// last iteration side by side, then the TV terms, then all sums. Each block runs the code of
+// the launch it stands for, so the sums are bitwise those of monitor and residual launches of
+// their own; three launches instead of five, whose small grids leave most of the chip idle
+// (256 x 256, L = 5: 28 and 11 us one after the other).
+template <int PIECE, bool ADD, typename DT>
+__global__ __launch_bounds__(MB) void k_check_pixel(IterArgs A, MonArgs D, MonPtrs M, ResPtrs R, int nbm) {
+  const int b = (int)blockIdx.x;
+  if (b < nbm)
+    mon_pixel_body<PIECE, ADD, DT>(A, D, M, b);
+  else
+    residuals_body<DT>(R, A, b - nbm, (int)gridDim.x - nbm);
+}
+__global__ __launch_bounds__(MB) void k_check_final(const double *part1, const double *part2, int nbm, double *mon,
+                                                    const double *rpart, int nbr, double *res) {
+  const int q = (int)blockIdx.x;
+  if (q < 7)
+    mon_final_body(part1, part2, nbm, mon, q);
+  else
+    sum_quads_body(rpart, nbr, res, q - 7);
+}
+template <int PIECE, bool ADD>
+void launch_check_t(const IterArgs &A, const MonArgs &D, const MonPtrs &M, const ResPtrs &R, int nbm, int nbr,
+                    hipStream_t st) {
+  if (M.bf16)
+    hipLaunchKernelGGL((k_check_pixel<PIECE, ADD, uint16_t>), dim3(nbm + nbr), dim3(MB), 0, st, A, D, M, R, nbm);
+  else
+    hipLaunchKernelGGL((k_check_pixel<PIECE, ADD, float>), dim3(nbm + nbr), dim3(MB), 0, st, A, D, M, R, nbm);
+}
+
 // Batched monitor: the blocks of every member of a list in one launch. first[l] is the first
 // block of list entry l (first[nl] the total), mem[l] its member; each block runs the lone
 // kernel's code on its member's parameters and block index, so every member's partial and
@@ -782,6 +813,26 @@ hipError_t launch_monitor(int piece, bool add, const IterArgs &A, const MonArgs 
   if ((e = hipGetLastError()) != hipSuccess) return e;
   hipLaunchKernelGGL(monitor_final, dim3(7), dim3(MB), 0, st, M.part1, M.part2, nb, M.final_);
   if (nb_out) *nb_out = nb;
+  return hipGetLastError();
+}
+
+static_assert(MB == RB, "a check's blocks run either body");
+
+hipError_t launch_check(int piece, bool add, const IterArgs &A, const MonArgs &D, const MonPtrs &M, const ResPtrs &R,
+                        double *res, hipStream_t st) {
+  const int nbm = monitor_blocks(A), nbr = residual_blocks(A);
+  if (piece == SLI_QUAD)
+    add ? launch_check_t<SLI_QUAD, true>(A, D, M, R, nbm, nbr, st) : launch_check_t<SLI_QUAD, false>(A, D, M, R, nbm, nbr, st);
+  else if (piece == SLI_TRUNC)
+    add ? launch_check_t<SLI_TRUNC, true>(A, D, M, R, nbm, nbr, st) : launch_check_t<SLI_TRUNC, false>(A, D, M, R, nbm, nbr, st);
+  else
+    launch_check_t<SLI_SAMPLED, false>(A, D, M, R, nbm, nbr, st);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(monitor_tv, dim3(nbm), dim3(MB), 0, st, A, D, M);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_check_final, dim3(7 + 4), dim3(MB), 0, st, M.part1, M.part2, nbm, M.final_,
+                     (const double *)R.part, nbr, res);
   return hipGetLastError();
 }
 

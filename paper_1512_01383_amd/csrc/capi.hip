@@ -110,8 +110,7 @@ struct Layout {
   size_t state_lo, state_hi;  // contiguous range holding u, s, v, z, p, qd
 };
 
-// lone: a problem of its own (with room for the on-chip iteration), not a batch member
-Layout make_layout(const sl_problem_desc *d, int nb_mon, bool lone) {
+Layout make_layout(const sl_problem_desc *d, int nb_mon) {
   Layout L{};
   const int k = d->L - 1;
   L.N = (long long)d->H * d->W;
@@ -162,8 +161,7 @@ Layout make_layout(const sl_problem_desc *d, int nb_mon, bool lone) {
   }
   L.off_rfin = take(32);
   L.base = o;
-  L.rim = lone ? resident_exchange_bytes(piece_of(d->rho), !sampled && d->samples, d->H, d->W, k,
-                                         band_most(d)) : 0;
+  L.rim = resident_exchange_bytes(piece_of(d->rho), !sampled && d->samples, d->H, d->W, k, band_most(d));
   L.off_rim = take(L.rim);
   L.total = o;
   return L;
@@ -538,8 +536,9 @@ sl_status band_quad(sl_problem_ *P) {
 constexpr int kResidentMin = 8;
 
 // `iters` iterations in one on-chip launch; *done is set if the problem and its stream allow
-// it (a stream that is being captured keeps the plain launches)
-sl_status resident_run(sl_problem_ *P, int iters, bool *done) {
+// it (a stream that is being captured keeps the plain launches). save: also keep the duals
+// before the last iteration, as save_duals does.
+sl_status resident_run(sl_problem_ *P, int iters, bool *done, bool save = false) {
   *done = false;
   ResidentPlan L;
   if (!P->resident || iters < kResidentMin ||
@@ -574,6 +573,14 @@ sl_status resident_run(sl_problem_ *P, int iters, bool *done) {
   R.so = P->sbuf(is);
   R.spo = P->sbuf(1 - is);
   R.po = P->pbuf(ip);
+  if (save) {
+    const size_t kd = (size_t)P->A.k * P->lay.ps * P->esz();
+    char *ys = P->ws + P->lay.off_ysave;
+    R.vsave = ys;
+    R.zsave = ys + kd;
+    R.qsave = (float *)(ys + 2 * kd);
+    R.psave = P->pbuf(1 - ip);
+  }
   R.fn = (const float *)(P->ws + P->lay.off_fn);
   R.wadd = (const float *)(P->ws + P->lay.off_w);
   R.cost = (const float *)(P->ws + P->lay.off_cost);
@@ -701,12 +708,6 @@ MonPtrs monitor_ptrs(sl_problem_ *P) {
   M.final_ = mon_out(P);
   M.bf16 = P->bf16;
   return M;
-}
-
-sl_status monitor_enqueue(sl_problem_ *P) {
-  const MonPtrs M = monitor_ptrs(P);
-  HIPCHK(launch_monitor(P->piece, P->add, P->A, P->D, M, P->st, nullptr), "monitor launch");
-  return SL_OK;
 }
 
 // Member lists of a batched check launch (0: members with bf16 duals, 1: with float duals,
@@ -871,13 +872,20 @@ sl_status pinned(sl_problem_ *P, size_t n, double **out) {
   return SL_OK;
 }
 
+// The sums of a check land in the pinned buffer itself (the kernels write it directly: a copy
+// of 56 bytes costs as much as a small kernel); without one (allocation-free problems) they
+// go to the workspace and are copied. stage[0 .. 6]: monitor, stage[8 .. 11]: residuals.
+constexpr size_t kStage = 16;
+
 sl_status monitor(sl_problem_ *P, sl_report *out) {
-  sl_status s = monitor_enqueue(P);
-  if (s != SL_OK) return s;
   double *stage = nullptr;
-  if ((s = pinned(P, SLI_NMON, &stage)) != SL_OK) return s;
-  HIPCHK(hipMemcpyAsync(stage, mon_out(P), 7 * sizeof(double), hipMemcpyDeviceToHost, P->st),
-         "monitor copy");
+  sl_status s = pinned(P, kStage, &stage);
+  if (s != SL_OK) return s;
+  MonPtrs M = monitor_ptrs(P);
+  if (!P->no_alloc) M.final_ = stage;
+  HIPCHK(launch_monitor(P->piece, P->add, P->A, P->D, M, P->st, nullptr), "monitor launch");
+  if (P->no_alloc)
+    HIPCHK(hipMemcpyAsync(stage, mon_out(P), 7 * sizeof(double), hipMemcpyDeviceToHost, P->st), "monitor copy");
   HIPCHK(hipStreamSynchronize(P->st), "monitor sync");
   memcpy(P->fin, stage, 7 * sizeof(double));
   return monitor_finish(P, out);
@@ -1403,6 +1411,33 @@ sl_status iterate_with_residuals(sl_problem_ *P, double *res) {
   return s;
 }
 
+// `iters` iterations, the last with its residuals in res (as iterate_with_residuals), and the
+// monitor's sums of the state after them in P->fin: one wait for both.
+sl_status iterate_and_check(sl_problem_ *P, int iters, double *res) {
+  bool done = false;
+  sl_status s = P->band_ws ? SL_OK : resident_run(P, iters, &done, true);
+  if (s == SL_OK && !done) {
+    s = enqueue_iters(P, iters - 1);
+    if (s == SL_OK) s = save_duals(P);
+    if (s == SL_OK) s = enqueue_iters(P, 1);
+  }
+  if (s != SL_OK) return s;
+  double *stage = nullptr;
+  if ((s = pinned(P, kStage, &stage)) != SL_OK) return s;
+  MonPtrs M = monitor_ptrs(P);
+  if (!P->no_alloc) M.final_ = stage;
+  double *const rout = P->no_alloc ? res_out(P) : stage + 8;
+  HIPCHK(launch_check(P->piece, P->add, P->A, P->D, M, residual_ptrs(P), rout, P->st), "check");
+  if (P->no_alloc) {
+    HIPCHK(hipMemcpyAsync(stage, mon_out(P), 7 * sizeof(double), hipMemcpyDeviceToHost, P->st), "check copy");
+    HIPCHK(hipMemcpyAsync(stage + 8, rout, 4 * sizeof(double), hipMemcpyDeviceToHost, P->st), "check copy");
+  }
+  HIPCHK(hipStreamSynchronize(P->st), "check sync");
+  memcpy(P->fin, stage, 7 * sizeof(double));
+  for (int j = 0; j < 4; j++) res[j] = stage[8 + j];
+  return SL_OK;
+}
+
 // Residual balancing (adaptive primal-dual method of Goldstein, Li, Yuan, Esser and
 // Baraniuk, cited in Sec. 4): a primal residual more than 1.5 times s times the dual one
 // enlarges the primal steps (c *= 1 - alpha), one below s times the dual one divided by 1.5
@@ -1567,7 +1602,7 @@ sl_status sl_workspace_size(const sl_problem_desc *desc, size_t *bytes) {
   if (!bytes) return fail(SL_ERR_INVALID_ARG, "bytes is NULL");
   sl_status s = validate(desc);
   if (s != SL_OK) return s;
-  *bytes = make_layout(desc, monitor_blocks_max((long long)desc->H * desc->W), true).total;
+  *bytes = make_layout(desc, monitor_blocks_max((long long)desc->H * desc->W)).total;
   return SL_OK;
 }
 
@@ -1579,7 +1614,7 @@ static sl_status init_impl(sl_problem_ *P, const sl_problem_desc *desc, void *ws
   if (s != SL_OK) return s;
   if (!ws || ((uintptr_t)ws & 255)) return fail(SL_ERR_WORKSPACE, "workspace NULL or not 256-byte aligned");
   const int nb_mon = monitor_blocks_max((long long)desc->H * desc->W);
-  Layout lay = make_layout(desc, nb_mon, true);
+  Layout lay = make_layout(desc, nb_mon);
   if (bytes < lay.base)
     return fail(SL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", bytes, lay.base);
   int dev = -1;
@@ -1705,16 +1740,20 @@ static sl_status single_run_to_gap(sl_problem_ *P, double rel_gap, int32_t max_i
   sl_report r;
   while (n < max_iters) {
     int chunk = std::min(P->check_every, max_iters - n);
-    sl_status s = enqueue_iters(P, P->d.adaptive_steps ? chunk - 1 : chunk);
-    if (s != SL_OK) return s;
+    sl_status s;
     if (P->d.adaptive_steps) {
       // the check interval's last iteration measures the residuals that steer the balance
       double res[4];
-      if ((s = iterate_with_residuals(P, res)) != SL_OK) return s;
+      if ((s = iterate_and_check(P, chunk, res)) != SL_OK) return s;
       adapt_balance(P, res);
+      n += chunk;
+      s = monitor_finish(P, &r);
+    } else {
+      if ((s = enqueue_iters(P, chunk)) != SL_OK) return s;
+      n += chunk;
+      s = monitor(P, &r);
     }
-    n += chunk;
-    if ((s = monitor(P, &r)) != SL_OK) {
+    if (s != SL_OK) {
       if (done) *done = n;
       return s;
     }
@@ -1788,7 +1827,7 @@ sl_status sl_batch_workspace_size(const sl_problem_desc *descs, int32_t n, size_
   for (int i = 0; i < n; i++) {
     sl_status s = validate(&descs[i]);
     if (s != SL_OK) return fail(s, "instance %d: %s", i, g_err.c_str());
-    total += align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W), false).total);
+    total += align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W)).total);
     maxtiles.push_back(max_tiles(descs[i].H, descs[i].W));
   }
   *bytes = total + batch_table_bytes(maxtiles, n);
@@ -1821,9 +1860,11 @@ sl_status sl_batch_create(const sl_problem_desc *descs, int32_t n, void *ws, siz
   size_t off = 0;
   std::vector<int> maxtiles;
   for (int i = 0; i < n; i++) {
-    const size_t sz = align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W), false).total);
+    const Layout lay = make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W));
+    const size_t sz = align256(lay.total);
     sl_problem q = nullptr;
-    s = create_impl(&descs[i], base + off, sz, stream, &q);
+    // (without the rim words: a batch's members advance together, launch by launch)
+    s = create_impl(&descs[i], base + off, lay.base, stream, &q);
     if (s != SL_OK) {
       delete B;
       return fail(s, "instance %d: %s", i, g_err.c_str());
@@ -2373,7 +2414,7 @@ sl_status sl_solve_static(const sl_problem_desc *desc, double rel_gap, int32_t m
   sl_status s = validate(desc);
   if (s != SL_OK) return s;
   // (a problem that fits without the on-chip iteration's rim words runs without them)
-  const size_t need = make_layout(desc, monitor_blocks_max((long long)desc->H * desc->W), true).base;
+  const size_t need = make_layout(desc, monitor_blocks_max((long long)desc->H * desc->W)).base;
   if (need > (size_t)SL_STATIC_WORKSPACE_BYTES)
     return fail(SL_ERR_UNSUPPORTED, "the problem needs %zu bytes of workspace; the allocation-free solve "
                 "has %zu", need, (size_t)SL_STATIC_WORKSPACE_BYTES);

@@ -36,6 +36,11 @@ struct ResBatch {
 };
 hipError_t launch_residuals_batch(const ResBatch &B, hipStream_t st);
 
+// One problem's check: launch_monitor and launch_residuals in three launches; the four residual
+// sums go to res, the seven of the monitor to M.final_.
+hipError_t launch_check(int piece, bool add, const IterArgs &A, const MonArgs &D, const MonPtrs &M, const ResPtrs &R,
+                        double *res, hipStream_t st);
+
 // block -> (list entry, block within its member) of a batched launch: first[0..nl] holds
 // each entry's first block; returns the member index mem[entry]
 __device__ __forceinline__ int member_block(const int *__restrict__ mem, const int *__restrict__ first, int nl,

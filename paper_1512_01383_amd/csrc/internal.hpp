@@ -121,6 +121,9 @@ struct ResidentArgs {
   const void *v, *z, *p;
   float *uo, *upo, *so, *spo, *qo;
   void *vo, *zo, *po;
+  // if not NULL: v, z, q and p as they were before the last iteration (p like po), for the residuals
+  void *vsave, *zsave, *psave;
+  float *qsave;
   const float *fn, *wadd, *cost;
   const float4 *tau;
   const unsigned *sinfo;

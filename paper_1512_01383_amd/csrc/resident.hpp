@@ -165,7 +165,9 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
   const bool on = r < H && n > 0;                  // uniform in the wave: it has work
   const bool col = c < W, in = r < H && col;
   const unsigned x = in ? (unsigned)(r * W + c) : 0u, xb = x * 4u;
-  auto in_row = [&](int rp) { return RP == 1 ? in : col && r + rp < H; };
+  // row rp of the thread is in the image: uniform in the wave, so that with `col` one lane mask
+  // serves all rows (a mask per row, kept in spilled scalar registers, came back wrong once)
+  auto row_in = [&](int rp) { return r + rp < H; };
   auto row_off = [&](int rp) { return RP == 1 ? xb : xb + 4u * (unsigned)(rp * W); };
   const bool top = on && ty == 0 && r0 > 0, bottom = on && ty == TH - 1 && r0 + TR < H;
   const bool halo = top || bottom;                 // a row of ubar beyond the tile enters
@@ -233,33 +235,43 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
 #pragma unroll
   for (int rp = 0; rp < RP; rp++) {
     const unsigned xr = row_off(rp);
-    const bool inr = in_row(rp);
-    q[rp] = inr ? ldb(R.q, xr) : 0.f;
-    fc[rp] = PIECE != SLI_SAMPLED && inr ? ldb(R.fn, xr) : 0.f;
+    q[rp] = fc[rp] = 0.f;
+    if (row_in(rp)) {
+      if (col) {
+        q[rp] = ldb(R.q, xr);
+        if (PIECE != SLI_SAMPLED) fc[rp] = ldb(R.fn, xr);
+      }
+    }
 #pragma unroll
     for (int j = 0; j < CH; j++) {
       if (E > 4) in_turn();
       const int e = rp * CH + j, i = i0 + j;
       u[e] = s[e] = v[e] = z[e] = px[e] = 0.f;
-      float ub = 0.f, sb = 0.f, py = 0.f;
-      if (inr && j < n) {
-        const long long o = (long long)i * ps;
-        u[e] = ldb(R.u + o, xr);
-        ub = 2.f * u[e] - ldb(R.up + o, xr);
-        s[e] = ldb(R.s + o, xr);
-        sb = 2.f * s[e] - ldb(R.sp + o, xr);
-        v[e] = ldd(R.v, i, xr);
-        z[e] = ldd(R.z, i, xr);
-        px[e] = ldd(R.p, i, xr);
-        py = ldd(R.p, k + i, xr);
+      float ub = 0.f, sb = 0.f, py = 0.f, hx = 0.f, hy = 0.f;
+      if (row_in(rp) && j < n) {
+        if (col) {
+          const long long o = (long long)i * ps;
+          u[e] = ldb(R.u + o, xr);
+          ub = 2.f * u[e] - ldb(R.up + o, xr);
+          s[e] = ldb(R.s + o, xr);
+          sb = 2.f * s[e] - ldb(R.sp + o, xr);
+          v[e] = ldd(R.v, i, xr);
+          z[e] = ldd(R.z, i, xr);
+          px[e] = ldd(R.p, i, xr);
+          py = ldd(R.p, k + i, xr);
+          if (rp == 0 && top) {
+            hx = ldd(R.p, i, xr - 4u * (unsigned)W);
+            hy = ldd(R.p, k + i, xr - 4u * (unsigned)W);
+          }
+        }
       }
       lub[e * LS] = ub;
       lsb[e * LS] = sb;
       lpy[e * LP] = py;
       if (ty == 0 && rp == 0) {
         lpy[((RP - 1) * CH + j) * LP - 64] = 0.f;   // above the image: times zero in div p
-        lhx[j * LH] = top && inr && j < n ? ldd(R.p, i, xr - 4u * (unsigned)W) : 0.f;
-        lhy[j * LH] = top && inr && j < n ? ldd(R.p, k + i, xr - 4u * (unsigned)W) : 0.f;
+        lhx[j * LH] = hx;
+        lhy[j * LH] = hy;
       }
     }
   }
@@ -286,8 +298,11 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
     __syncthreads();
 #pragma unroll
     for (int rp = 0; rp < RP; rp++) {
-      const bool inr = in_row(rp);
-      const unsigned info = inr ? ldb(R.sinfo, row_off(rp)) : 31u | (31u << 13);
+      const bool inr = col && row_in(rp);
+      unsigned info = 31u | (31u << 13);
+      if (row_in(rp)) {
+        if (col) info = ldb(R.sinfo, row_off(rp));
+      }
       const int s0 = (int)(info & 31u), s1 = (int)((info >> 13) & 31u);
       const float lo = fc[rp] - R.del, hb = fc[rp] + R.del;
       int first = k;
@@ -353,9 +368,42 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
   const int bc = (nc + 63) / 64, batches = bc + (nq + 63) / 64, waves = (int)blockDim.x >> 6;
   publish(R.tag);
 
+  // a dual into plane i of `base`, at byte offset off of a float plane
+  auto std_ = [&](void *base, int i, unsigned off, float val) {
+    if (bf16)
+      stvb((uint16_t *)base + (long long)i * ps, off / 2, val);
+    else
+      stvb((float *)base + (long long)i * ps, off, val);
+  };
+  // what the residuals of the last iteration compare with: the duals before it
+  auto save_duals = [&] {
+    int is = i0;   // addresses formed here, not ahead of all iterations
+    unsigned xs = xb;
+    asm volatile("" : "+s"(is), "+v"(xs));
+#pragma unroll
+    for (int rp = 0; rp < RP; rp++) {
+      if (!row_in(rp)) continue;
+      const unsigned xr = RP == 1 ? xs : xs + 4u * (unsigned)(rp * W);
+      if (col) {
+#pragma unroll
+        for (int j = 0; j < CH; j++) {
+          if (j >= n) continue;
+          in_turn();
+          const int e = rp * CH + j, i = is + j;
+          std_(R.vsave, i, xr, v[e]);
+          std_(R.zsave, i, xr, z[e]);
+          std_(R.psave, i, xr, px[e]);
+          std_(R.psave, k + i, xr, lpy[e * LP]);
+        }
+        if (gp == 0) stb(R.qsave, xr, q[rp]);
+      }
+    }
+  };
   bool dead = false;
+  int it = 1, stop = R.vsave ? R.iters - 1 : R.iters;
+  while (true) {
 #pragma unroll 1
-  for (int it = 1; it <= R.iters; it++) {
+  for (; it <= stop; it++) {
     // values of one label or pixel that no iteration changes are formed where they are used:
     // hoisted out of the loop by the compiler they would take a register each and spill
     int ii = i0;
@@ -365,6 +413,7 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
     // so every sum's share, and nothing is stored
     const ResidentLabel *const lab = R.lab + ii;
     const float *fn = R.fn;
+    const unsigned nb4 = 4u * (unsigned)(H * W);
     int rr = r;
     unsigned xo = xb;
     if (RP > 1) asm volatile("" : "+s"(fn), "+s"(rr), "+v"(xo));
@@ -570,9 +619,10 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
       for (int rp = 0; rp < RP; rp++) {
         row_by_row();
         float pre = 0.f, rlast = 0.f;   // pre: sum of the new v of the label group so far
-        // the data centre: kept, or with several rows loaded again (registers are dearer)
+        // the data centre: kept, or with several rows loaded again (registers are dearer; rows
+        // past the image read 0)
         float f = fc[0];
-        if (PIECE == SLI_QUAD && RP > 1) f = col && rr + rp < H ? ldb(fn, xo + 4u * (unsigned)(rp * W)) : 0.f;
+        if (PIECE == SLI_QUAD && RP > 1) f = bld(fn, nb4, xo + 4u * (unsigned)(rp * W));
 #pragma unroll
         for (int j = 0; j < CH; j++) {
           const int e = rp * CH + j;
@@ -695,37 +745,38 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
     }
   }
 
+  if (it > R.iters) break;
+  save_duals();
+  stop = R.iters;
+  }
+
   // ---- the state back to memory (after a wait that was given up: no state, but NaN)
   if (dead) {
 #pragma unroll
     for (int e = 0; e < E; e++) u[e] = __builtin_nanf("");
   }
-  auto std_ = [&](void *base, int i, unsigned off, float val) {
-    if (bf16)
-      stvb((uint16_t *)base + (long long)i * ps, off / 2, val);
-    else
-      stvb((float *)base + (long long)i * ps, off, val);
-  };
 #pragma unroll
   for (int rp = 0; rp < RP; rp++) {
-    if (!in_row(rp)) continue;
+    if (!row_in(rp)) continue;
     const unsigned xr = row_off(rp);
+    if (col) {
 #pragma unroll
-    for (int j = 0; j < CH; j++) {
-      if (j >= n) continue;
-      if (E > 4) in_turn();
-      const int e = rp * CH + j, i = i0 + j;
-      const long long o = (long long)i * ps;
-      stb(R.uo + o, xr, u[e]);
-      stb(R.upo + o, xr, lub[e * LS]);
-      stb(R.so + o, xr, s[e]);
-      stb(R.spo + o, xr, lsb[e * LS]);
-      std_(R.vo, i, xr, v[e]);
-      std_(R.zo, i, xr, z[e]);
-      std_(R.po, i, xr, px[e]);
-      std_(R.po, k + i, xr, lpy[e * LP]);
+      for (int j = 0; j < CH; j++) {
+        if (j >= n) continue;
+        if (E > 4) in_turn();
+        const int e = rp * CH + j, i = i0 + j;
+        const long long o = (long long)i * ps;
+        stb(R.uo + o, xr, u[e]);
+        stb(R.upo + o, xr, lub[e * LS]);
+        stb(R.so + o, xr, s[e]);
+        stb(R.spo + o, xr, lsb[e * LS]);
+        std_(R.vo, i, xr, v[e]);
+        std_(R.zo, i, xr, z[e]);
+        std_(R.po, i, xr, px[e]);
+        std_(R.po, k + i, xr, lpy[e * LP]);
+      }
+      if (gp == 0) stb(R.qo, xr, q[rp]);
     }
-    if (gp == 0) stb(R.qo, xr, q[rp]);
   }
 }
 
