@@ -140,6 +140,8 @@ def _torch():
 def _dev_f32(a, device):
     torch = _torch()
     if isinstance(a, torch.Tensor):
+        if a.dtype is torch.float32 and a.device == device and a.is_contiguous():
+            return a   # what .to() and .contiguous() would return, without their dispatch
         return a.to(device=device, dtype=torch.float32).contiguous()
     return torch.as_tensor(np.ascontiguousarray(a, dtype=np.float32), device=device)
 
@@ -453,15 +455,13 @@ def stereo_costs(left, right, D: int, trunc: float, out=None, device=None):
     torch's current stream."""
     torch = _torch()
     dev = torch.device(device if device is not None else "cuda:0")
-    lt = _dev_f32(left, dev).contiguous()
-    rt = _dev_f32(right, dev).contiguous()
+    lt = _dev_f32(left, dev)
+    rt = _dev_f32(right, dev)
     H, W = lt.shape
     if out is None:
         out = torch.empty((int(D), H, W), dtype=torch.float32, device=dev)
-    stream = torch.cuda.current_stream(dev)
-    _check(lib().sl_stereo_costs(C.c_void_p(lt.data_ptr()), C.c_void_p(rt.data_ptr()), H, W, int(D),
-                                 float(trunc), C.c_void_p(out.data_ptr()),
-                                 C.c_void_p(stream.cuda_stream)))
+    _check(lib().sl_stereo_costs(lt.data_ptr(), rt.data_ptr(), H, W, int(D), float(trunc), out.data_ptr(),
+                                 torch.cuda.current_stream(dev).cuda_stream))
     return out   # lt / rt may be released: the allocator orders their reuse on this stream
 
 
