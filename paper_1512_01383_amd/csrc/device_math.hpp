@@ -209,67 +209,49 @@ __device__ __forceinline__ void proj_quad(float a, float ia, float c, float g0, 
 
 // A part's wave-uniform constants come from a per-sample table: its slope t, 1/(1 + t^2)
 // (the foot of the perpendicular) and 1/(t - t_prev) (the kink with the previous part).
-// The scan decides the region and keeps the conjugate's value at y0 (the maximum over the
-// parts: is the point below the graph?); the nearest-point fallback for a point that
-// rounding leaves in no region runs as a second pass over the parts (PLNear). Each region
-// test is one comparison of a three-way minimum and its outcome a select, so the scan runs
-// on the vector unit alone (no lane-mask arithmetic or branches per part); the regions are
-// disjoint, so a later hit replaces an earlier one only where rounding puts the point on a
-// shared boundary, where both answers agree up to rounding.
+// Along the graph the regions are ordered: strip, cone, strip, cone, .. So one comparison per
+// kink (does the point lie to the right of the strip before it?) is true up to the point's
+// region and false after it, and the scan only has to keep, by selects, the last kink passed
+// and the part after it; whether the point sits in that kink's cone or in that part's strip,
+// and the foot, are worked out once at the end. 15 vector operations a kink, against 26 for
+// testing strip and cone of every part. Where rounding puts neighbouring kinks out of order the
+// answers coincide up to rounding. The scan also keeps the conjugate's value at y0 (the
+// maximum over the parts: is the point below the graph?).
+// On chip, 288x384 with 64 samples and 7 intervals: 13.8 us an iteration with the tests of
+// every part, 12.6 with this scan, 9.5 with its samples loaded ahead and the places past a
+// label's last sample made harmless instead of branched around.
 struct PLScan {
-  float y0, w0, gmax, lo, tp, cp, irp, ay, aw, fnd;
-  bool has;
-  __device__ __forceinline__ void init(float y, float w) {
+  float y0, w0, gmax, bl, gl, t, r, ir, tp, cp;
+  __device__ __forceinline__ void first(float y, float w, const float4 &T, float r0) {
     y0 = y;
     w0 = w;
-    gmax = -SL_INF;
-    lo = -SL_INF;
-    tp = cp = irp = 0.f;
-    ay = y;
-    aw = w;
-    fnd = 0.f;
-    has = false;
+    gmax = T.x * y0 - r0;
+    bl = -SL_INF;
+    gl = 0.f;
+    t = tp = T.x;
+    r = cp = r0;
+    ir = T.y;
   }
-  // the previous part (slope tp through (., -cp)) on [lo, hi]: does the point lie in its
-  // strip (foot on the part, point below the line)?
-  __device__ __forceinline__ void seg(float hi) {
-    const float mu = (tp * y0 - cp - w0) * irp;   // >= 0: point below the line
-    const float yr = y0 - mu * tp;                // perpendicular foot
-    const bool hit = fminf(fminf(mu, yr - lo), hi - yr) >= 0.f;
-    ay = hit ? yr : ay;
-    aw = hit ? tp * yr - cp : aw;
-    fnd = hit ? 1.f : fnd;
-  }
-  // kink at y = b between the previous part and the part of slope t1: its normal cone is
-  // {(b, g(b)) + a (tp, -1) + c (t1, -1) : a, c >= 0}
-  __device__ __forceinline__ void kink(float b, float t1) {
+  __device__ __forceinline__ void push(const float4 &T, float r1) {
+    gmax = fmaxf(gmax, T.x * y0 - r1);
+    const float b = (r1 - cp) * T.z;   // kink between the previous part and this one
     const float gb = tp * b - cp;
-    const float dw = gb - w0, dy = y0 - b;
-    const bool hit = fminf(fminf(dw, dy - tp * dw), t1 * dw - dy) >= 0.f;
-    ay = hit ? b : ay;
-    aw = hit ? gb : aw;
-    fnd = hit ? 1.f : fnd;
-  }
-  __device__ __forceinline__ void push(const float4 &T, float r) {
-    gmax = fmaxf(gmax, T.x * y0 - r);
-    if (has) {
-      const float b = (r - cp) * T.z;
-      seg(b);
-      kink(b, T.x);
-      lo = b;
-    }
+    const bool right = y0 - b > tp * fmaxf(gb - w0, 0.f);
+    bl = right ? b : bl;
+    gl = right ? gb : gl;
+    t = right ? T.x : t;
+    r = right ? r1 : r;
+    ir = right ? T.y : ir;
     tp = T.x;
-    cp = r;
-    irp = T.y;
-    has = true;
+    cp = r1;
   }
-  // true when the point lies below the graph but in no region (the caller then runs PLNear)
-  __device__ __forceinline__ bool finish(float &y, float &w) {
-    seg(SL_INF);
+  __device__ __forceinline__ void finish(float &y, float &w) {
+    const bool cone = !(y0 - bl > t * fmaxf(gl - w0, 0.f));
+    const float mu = (t * y0 - r - w0) * ir;
+    const float yr = y0 - mu * t;   // perpendicular foot
     const bool out = w0 < gmax;
-    y = out ? ay : y;
-    w = out ? aw : w;
-    return out && fnd == 0.f;
+    w = out ? (cone ? gl : t * yr - r) : w;
+    y = out ? (cone ? bl : yr) : y;
   }
 };
 
@@ -280,52 +262,9 @@ struct PLScan {
 typedef float sl_f32x4 __attribute__((ext_vector_type(4)));
 typedef const __attribute__((address_space(4))) sl_f32x4 sl_const_f32x4;
 __device__ __forceinline__ float4 ldtab(const float4 *tab, int m) {
-  const sl_f32x4 v = ((sl_const_f32x4 *)tab)[m];
+  const sl_f32x4 v = ((sl_const_f32x4 *)tab)[(unsigned)m];
   return make_float4(v.x, v.y, v.z, v.w);
 }
-
-// nearest point of the graph among the nearest points of its parts
-struct PLNear {
-  float y0, w0, bd, by, bw, lo, tp, cp, irp;
-  bool has;
-  __device__ __forceinline__ void init(float y, float w) {
-    y0 = y;
-    w0 = w;
-    bd = SL_INF;
-    by = y;
-    bw = w;
-    lo = -SL_INF;
-    tp = cp = irp = 0.f;
-    has = false;
-  }
-  __device__ __forceinline__ void part(float hi) {
-    const float mu = (tp * y0 - cp - w0) * irp;
-    const float yf = fminf(fmaxf(y0 - mu * tp, lo), hi);
-    const float wf = tp * yf - cp;
-    const float d = (yf - y0) * (yf - y0) + (wf - w0) * (wf - w0);
-    if (d < bd) {
-      bd = d;
-      by = yf;
-      bw = wf;
-    }
-  }
-  __device__ __forceinline__ void push(const float4 &T, float r) {
-    if (has) {
-      const float b = (r - cp) * T.z;
-      part(b);
-      lo = b;
-    }
-    tp = T.x;
-    cp = r;
-    irp = T.y;
-    has = true;
-  }
-  __device__ __forceinline__ void finish(float &y, float &w) {
-    part(SL_INF);
-    y = by;
-    w = bw;
-  }
-};
 
 // Truncated quadratic on a straddling interval: samples t_m = g0 + m (g1-g0)/15
 // (t_0 = g0, t_15 = g1) with values min(a/2 (t_m - c)^2, nu). Samples inside the band lie

@@ -501,8 +501,7 @@ __device__ __forceinline__ void iter_tile(const IterPtrs<DT> &P, const IterArgs 
           const int m1 = __builtin_amdgcn_readfirstlane(A.sidx[i + 1]);
           const unsigned xe = xm + 4u * (unsigned)e;
           PLScan pl;
-          pl.init(y, w);
-          pl.push(ldtab(P.tau, m0), i > i0 ? rlast[e] : bld(P.cost + (size_t)(m0) * ps, nb4, xe));
+          pl.first(y, w, ldtab(P.tau, m0), i > i0 ? rlast[e] : bld(P.cost + (size_t)(m0) * ps, nb4, xe));
           float4 tq[kSmp];   // table entries, all requested before the first is used
 #pragma unroll
           for (int q = 0; q < kSmp; q++) tq[q] = ldtab(P.tau, min(m0 + 1 + q, m1));
@@ -522,12 +521,7 @@ __device__ __forceinline__ void iter_tile(const IterPtrs<DT> &P, const IterArgs 
               if (mb + q <= m1) pl.push(tr[q], rr[q]);
           }
           rlast[e] = pl.cp;
-          if (pl.finish(y, w)) {   // rare: no region holds the point (rounding)
-            PLNear nn;
-            nn.init(y, w);
-            for (int m = m0; m <= m1; m++) nn.push(ldtab(P.tau, m), bld(P.cost + (size_t)(m) * ps, nb4, xe));
-            nn.finish(y, w);
-          }
+          pl.finish(y, w);
         }
         if (ADD) {
           y += bs;

@@ -401,6 +401,13 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
   };
   bool dead = false;
   int it = 1, stop = R.vsave ? R.iters - 1 : R.iters;
+  // samples: the prologue's loads end here; left pending, the compiler would wait, in every
+  // iteration, at the first use of these for whatever else is in flight
+  if constexpr (PIECE == SLI_SAMPLED) {
+#pragma unroll
+    for (int e = 0; e < E; e++) asm volatile("" : "+v"(v[e]), "+v"(z[e]), "+v"(px[e]));
+    asm volatile("" : "+v"(q[0]), "+v"(pxL), "+v"(pyL), "+v"(radL));
+  }
   while (true) {
 #pragma unroll 1
   for (; it <= stop; it++) {
@@ -528,6 +535,27 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
     };
     float pre_[LG];   // sums of the new v per label group
     float wlo[ADD ? CH + 1 : 1];   // additive values at the thread's labels
+    // samples: those of the label at work and, a batch of NS ahead of their use, the next ones
+    // (mb on, up to the last one `most`); a label starts with the last sample of the one before
+    constexpr int NS = 5;
+    float rnext[NS], rfirst = 0.f;
+    int mb = 0;
+    auto cost = [&](int m) {
+      return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(plane_rsrc(R.cost, 0x7fffffffu), (int)xb,
+                                                                            (int)(4u * (unsigned)ps * (unsigned)m), 0));
+    };
+    auto samples = [&](int most) {
+#pragma unroll
+      for (int m = 0; m < NS; m++) rnext[m] = cost(min(mb + m, most));
+    };
+    auto last_sample = [&](int i) { return __builtin_amdgcn_readfirstlane(R.sidx[i + 1]); };
+    if (PIECE == SLI_SAMPLED && on && n > 0) {
+      mb = __builtin_amdgcn_readfirstlane(R.sidx[i0]);
+      rfirst = cost(mb);
+      mb++;
+      samples(last_sample(i0));
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if (on) {
       if (ADD) {
 #pragma unroll
@@ -618,7 +646,7 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
 #pragma unroll
       for (int rp = 0; rp < RP; rp++) {
         row_by_row();
-        float pre = 0.f, rlast = 0.f;   // pre: sum of the new v of the label group so far
+        float pre = 0.f;   // sum of the new v of the label group so far
         // the data centre: kept, or with several rows loaded again (registers are dearer; rows
         // past the image read 0)
         float f = fc[0];
@@ -640,31 +668,28 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
               w = lw[(rp * slots + i0 + j - lfirst[rp]) * NP];
             }
           } else if (j < n) {
-            const int m0 = __builtin_amdgcn_readfirstlane(R.sidx[i0 + j]);
-            const int m1 = __builtin_amdgcn_readfirstlane(R.sidx[i0 + j + 1]);
-            auto cost = [&](int m) { return ldb(R.cost + (long long)m * ps, xb); };
+            // a batch's places past the label's last sample repeat it; the kink of the sample with
+            // itself is put at 0 times infinity, which lies right of no point
+            const int m1 = last_sample(i0 + j), m2 = last_sample(min(i0 + j + 1, k - 1));
             PLScan pl;
-            pl.init(y, w);
-            pl.push(ldtab(R.tau, m0), j > 0 ? rlast : cost(m0));
-            for (int mb = m0 + 1; mb <= m1; mb += 8) {
-              float rr[8];
-              float4 tq[8];
+            pl.first(y, w, ldtab(R.tau, mb - 1), rfirst);
+            while (mb <= m1) {
+              float rr[NS];
+              float4 tq[NS];
 #pragma unroll
-              for (int m = 0; m < 8; m++) {
-                rr[m] = cost(min(mb + m, m1));
+              for (int m = 0; m < NS; m++) {
+                rr[m] = rnext[m];
                 tq[m] = ldtab(R.tau, min(mb + m, m1));
+                if (mb + m > m1) tq[m].z = SL_INF;
               }
+              mb = min(mb + NS, m1 + 1);
+              samples(mb <= m1 ? m1 : m2);
+              __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-              for (int m = 0; m < 8; m++)
-                if (mb + m <= m1) pl.push(tq[m], rr[m]);
+              for (int m = 0; m < NS; m++) pl.push(tq[m], rr[m]);
+              rfirst = rr[NS - 1];
             }
-            rlast = pl.cp;
-            if (pl.finish(y, w)) {   // rare: no region holds the point (rounding)
-              PLNear nn;
-              nn.init(y, w);
-              for (int m = m0; m <= m1; m++) nn.push(ldtab(R.tau, m), cost(m));
-              nn.finish(y, w);
-            }
+            pl.finish(y, w);
           }
           if (ADD) {
             const float bs = (wlo[ADD ? j + 1 : 0] - wlo[ADD ? j : 0]) * lab[j].ih;
