@@ -2109,14 +2109,17 @@ sl_status sl_unrolled_forward(sl_problem P, int32_t K, int32_t C, void *ws, size
   for (int c = 0; c < U.ncp; c++) {
     // checkpoint c: [up][u][sp][s][v][z][q][px][py] of the state before iteration c*C
     char *ck = w + U.ckpt + (size_t)c * (8 * k + 1) * pl;
-    const void *src[7] = {P->ubuf((P->iu + 2) % 3), P->ubuf(P->iu), P->sbuf(1 - P->is), P->sbuf(P->is),
-                          P->ws + P->lay.off_v, P->ws + P->lay.off_z, P->ws + P->lay.off_qd};
-    const int np[7] = {k, k, k, k, k, k, 1};
-    for (int g = 0; g < 7; g++) {
-      HIPCHK(hipMemcpyAsync(ck, src[g], np[g] * pl, hipMemcpyDeviceToDevice, P->st), "checkpoint");
+    const void *src[8] = {P->ubuf((P->iu + 2) % 3), P->ubuf(P->iu), P->sbuf(1 - P->is), P->sbuf(P->is),
+                          P->ws + P->lay.off_v, P->ws + P->lay.off_z, P->ws + P->lay.off_qd, P->pbuf(P->ip)};
+    const int np[8] = {k, k, k, k, k, k, 1, 2 * k};
+    PlaneCopies copies;
+    for (int g = 0; g < 8; g++) {
+      copies.src[g] = src[g];
+      copies.dst[g] = ck;
+      copies.n[g] = np[g] * P->lay.ps;
       ck += np[g] * pl;
     }
-    HIPCHK(hipMemcpyAsync(ck, P->pbuf(P->ip), 2 * k * pl, hipMemcpyDeviceToDevice, P->st), "checkpoint");
+    HIPCHK(launch_plane_copies(copies, 8, P->st), "checkpoint");
     s = enqueue_iters(P, std::min(C, K - c * C), kSameBits);   // the replay's configuration
     if (s != SL_OK) return s;
   }
@@ -2164,18 +2167,18 @@ sl_status sl_unrolled_backward(sl_problem P, const float *grad_u, float *grad_f,
   float *useq = (float *)(w + U.useq), *sseq = (float *)(w + U.sseq);
   char *yseq = w + U.yseq;
   const size_t yslot = (size_t)(4 * k + 1) * pl;
-  auto uslot = [&](int j) { return useq + (size_t)j * k * ps; };   // u_{j-1}
-  auto sslot = [&](int j) { return sseq + (size_t)j * k * ps; };
-  auto yv = [&](int j) { return (float *)(yseq + (size_t)j * yslot); };
+  // a segment's states; the first one (u_{-1}, u_0, s_{-1}, s_0 and the duals of state 0) is read
+  // where it lies in its checkpoint, the replay writes the others
+  float *cp = nullptr;
+  auto uslot = [&](int j) { return (j < 2 ? cp : useq) + (size_t)j * k * ps; };   // u_{j-1}
+  auto sslot = [&](int j) { return j < 2 ? cp + (size_t)(2 + j) * k * ps : sseq + (size_t)j * k * ps; };
+  auto yv = [&](int j) { return j == 0 ? cp + (size_t)4 * k * ps : (float *)(yseq + (size_t)j * yslot); };
   auto yz = [&](int j) { return yv(j) + (size_t)k * ps; };
   auto yq = [&](int j) { return yv(j) + (size_t)2 * k * ps; };
   auto yp = [&](int j) { return yv(j) + (size_t)(2 * k + 1) * ps; };
   for (int c = U.ncp - 1; c >= 0; c--) {
     const int n = std::min(C, K - c * C);
-    const char *ck = w + U.ckpt + (size_t)c * (8 * k + 1) * pl;
-    HIPCHK(hipMemcpyAsync(uslot(0), ck, 2 * k * pl, hipMemcpyDeviceToDevice, P->st), "restore");
-    HIPCHK(hipMemcpyAsync(sslot(0), ck + 2 * k * pl, 2 * k * pl, hipMemcpyDeviceToDevice, P->st), "restore");
-    HIPCHK(hipMemcpyAsync(yv(0), ck + 4 * k * pl, yslot, hipMemcpyDeviceToDevice, P->st), "restore");
+    cp = (float *)(w + U.ckpt + (size_t)c * (8 * k + 1) * pl);
     // replay the segment, keeping every state (same launch configuration as the forward
     // pass): each iteration reads state j from its slots and writes state j + 1 to the next
     for (int j = 0; j + 1 < n; j++) {
