@@ -279,6 +279,14 @@ __device__ __forceinline__ float tau_of(int r, int c, int H, int W, float tau_c)
   return tau_c / (1.f + (float)deg);
 }
 
+// Workgroups go to the eight XCDs in turn; each XCD is given a contiguous part of the image, so
+// that the row below, which another block reads as its own, is in the same L2 (256x256, 8 labels,
+// 200 iterations forward and back: 8112 us with blocks in image order, 7908 so).
+__device__ __forceinline__ int tile_of_block() {
+  const int b = (int)blockIdx.x, nb = (int)gridDim.x, q = nb / 8, x = b % 8;
+  return x * q + min(x, nb % 8) + b / 8;
+}
+
 // ------------------------------------------------------------------ kernel 1: steps 1-4
 //
 // A block covers 64 consecutive pixels (one wavefront) times T label chunks (one wavefront
@@ -304,7 +312,7 @@ __global__ __launch_bounds__(64 * T) void k_adj_dual(AdjState X, AdjBuf B, AdjAc
   const long long ps = A.ps;
   const int lane = (int)(threadIdx.x & 63);
   const int t = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int xi = (int)blockIdx.x * 64 + lane;
+  const int xi = tile_of_block() * 64 + lane;
   const bool in = xi < H * W;
   const int r = in ? xi / W : 0, c = in ? xi - r * W : 0;
   const long long x = in ? xi : 0;
@@ -566,7 +574,7 @@ __global__ __launch_bounds__(64 * T) void k_adj_primal(AdjBuf B, IterArgs A) {
   const long long ps = A.ps;
   const int lane = (int)(threadIdx.x & 63);
   const int t = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  const int xi = (int)blockIdx.x * 64 + lane;
+  const int xi = tile_of_block() * 64 + lane;
   const bool in = xi < H * W;
   const int r = in ? xi / W : 0, c = in ? xi - r * W : 0;
   const long long x = in ? xi : 0;
