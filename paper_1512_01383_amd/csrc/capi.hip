@@ -535,15 +535,15 @@ sl_status band_quad(sl_problem_ *P) {
 // saves 3 us on the smallest problems and more on larger ones.
 constexpr int kResidentMin = 8;
 
-// `iters` iterations in one on-chip launch; *done is set if the problem and its stream allow
-// it (a stream that is being captured keeps the plain launches). save: also keep the duals
-// before the last iteration, as save_duals does.
-sl_status resident_run(sl_problem_ *P, int iters, bool *done, bool save = false) {
-  *done = false;
-  ResidentPlan L;
+// May `iters` iterations with the label groups of configuration cfg run on chip now (the problem
+// fits, the stream is not being captured)? Then its plan and the launch's arguments but for the state.
+sl_status resident_prepare(sl_problem_ *P, int iters, int cfg, const IterArgs &A, bool *ok, ResidentPlan *plan,
+                           ResidentArgs *args) {
+  *ok = false;
+  ResidentPlan &L = *plan;
   if (!P->resident || iters < kResidentMin ||
-      !resident_plan(P->piece, P->add, P->A.H, P->A.W, P->A.k, kIterCfg[P->cfg][0], P->qmax, P->cus, &L) ||
-      resident_rim_bytes(L, P->A.k) > P->lay.rim)
+      !resident_plan(P->piece, P->add, A.H, A.W, A.k, kIterCfg[cfg][0], P->qmax, P->cus, &L) ||
+      resident_rim_bytes(L, A.k) > P->lay.rim)
     return SL_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(P->st, &cap) != hipSuccess) {
@@ -556,9 +556,67 @@ sl_status resident_run(sl_problem_ *P, int iters, bool *done, bool save = false)
     HIPCHK(launch_fill_zero(rim, P->lay.rim, P->st), "rim words");
     P->rim_tag = 1;
   }
-  const IterArgs &A = P->A;
-  ResidentArgs R;
+  ResidentArgs &R = *args;
   memset(&R, 0, sizeof R);
+  R.fn = (const float *)(P->ws + P->lay.off_fn);
+  R.wadd = (const float *)(P->ws + P->lay.off_w);
+  R.cost = (const float *)(P->ws + P->lay.off_cost);
+  R.tau = (const float4 *)(P->ws + P->lay.off_tau);
+  R.sinfo = (const unsigned *)(P->ws + P->lay.off_sinfo);
+  R.ex = (unsigned long long *)rim;
+  R.err = (unsigned *)(P->ws + P->lay.off_flag) + 1;
+  R.ps = A.ps;
+  R.H = A.H;
+  R.W = A.W;
+  R.k = A.k;
+  R.G = kIterCfg[cfg][0];
+  R.TH = L.th;
+  R.iters = iters;
+  R.tag = P->rim_tag;
+  R.sig_p = A.sig_p;
+  R.sig_q = A.sig_q;
+  R.tau_c = A.tau_c;
+  R.lam = A.lam;
+  R.a = A.a;
+  R.ia = A.ia;
+  R.nu = A.nu;
+  R.del = A.del;
+  R.per = A.per;
+  R.iper = A.iper;
+  R.aniso = A.aniso;
+  R.bf16 = P->bf16;
+  R.qmax = P->qmax;
+  R.slots = L.slots;
+  for (int j = 0; j <= A.k; j++) R.sidx[j] = A.sidx[j];
+  for (int i = 0; i < A.k; i++)
+    R.lab[i] = {A.gam[i], A.gam[i + 1], A.h[i], A.ih[i], A.sig[i], A.taus[i], A.ig0[i], A.ig1[i]};
+  *ok = true;
+  return SL_OK;
+}
+
+sl_status resident_launch(sl_problem_ *P, const ResidentPlan &L, const ResidentArgs &R, bool *done) {
+  const hipError_t e = launch_resident(P->piece, P->add, L, R, P->st);
+  if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
+    (void)hipGetLastError();
+    P->resident = false;   // fewer blocks fit here than the plan assumes: plain launches
+    return SL_OK;
+  }
+  if (e != hipSuccess) return hip_fail(e, "on-chip iterations launch");
+  P->rim_tag += (unsigned)R.iters + 1u;
+  *done = true;
+  return SL_OK;
+}
+
+// `iters` iterations in one on-chip launch; *done is set if the problem and its stream allow
+// it (a stream that is being captured keeps the plain launches). save: also keep the duals
+// before the last iteration, as save_duals does.
+sl_status resident_run(sl_problem_ *P, int iters, bool *done, bool save = false) {
+  *done = false;
+  bool ok = false;
+  ResidentPlan L;
+  ResidentArgs R;
+  sl_status s = resident_prepare(P, iters, P->cfg, P->A, &ok, &L, &R);
+  if (s != SL_OK || !ok) return s;
   R.u = P->ubuf(P->iu);
   R.up = P->ubuf((P->iu + 2) % 3);
   R.s = P->sbuf(P->is);
@@ -581,51 +639,12 @@ sl_status resident_run(sl_problem_ *P, int iters, bool *done, bool save = false)
     R.qsave = (float *)(ys + 2 * kd);
     R.psave = P->pbuf(1 - ip);
   }
-  R.fn = (const float *)(P->ws + P->lay.off_fn);
-  R.wadd = (const float *)(P->ws + P->lay.off_w);
-  R.cost = (const float *)(P->ws + P->lay.off_cost);
-  R.tau = (const float4 *)(P->ws + P->lay.off_tau);
-  R.sinfo = (const unsigned *)(P->ws + P->lay.off_sinfo);
-  R.ex = (unsigned long long *)rim;
-  R.err = (unsigned *)(P->ws + P->lay.off_flag) + 1;
-  R.ps = A.ps;
-  R.H = A.H;
-  R.W = A.W;
-  R.k = A.k;
-  R.G = kIterCfg[P->cfg][0];
-  R.TH = L.th;
-  R.iters = iters;
-  R.tag = P->rim_tag;
-  R.sig_p = A.sig_p;
-  R.sig_q = A.sig_q;
-  R.tau_c = A.tau_c;
-  R.lam = A.lam;
-  R.a = A.a;
-  R.ia = A.ia;
-  R.nu = A.nu;
-  R.del = A.del;
-  R.per = A.per;
-  R.iper = A.iper;
-  R.aniso = A.aniso;
-  R.bf16 = P->bf16;
-  R.qmax = P->qmax;
-  R.slots = L.slots;
-  for (int j = 0; j <= A.k; j++) R.sidx[j] = A.sidx[j];
-  for (int i = 0; i < A.k; i++)
-    R.lab[i] = {A.gam[i], A.gam[i + 1], A.h[i], A.ih[i], A.sig[i], A.taus[i], A.ig0[i], A.ig1[i]};
-  const hipError_t e = launch_resident(P->piece, P->add, L, R, P->st);
-  if (e == hipErrorCooperativeLaunchTooLarge || e == hipErrorNotSupported) {
-    (void)hipGetLastError();
-    P->resident = false;   // fewer blocks fit here than the plan assumes: plain launches
-    return SL_OK;
-  }
-  if (e != hipSuccess) return hip_fail(e, "on-chip iterations launch");
-  P->rim_tag += (unsigned)iters + 1u;
+  s = resident_launch(P, L, R, done);
+  if (s != SL_OK || !*done) return s;
   P->iu = iu;
   P->is = is;
   P->ip = ip;
   P->iters += iters;
-  *done = true;
   return SL_OK;
 }
 
@@ -2181,7 +2200,38 @@ sl_status sl_unrolled_backward(sl_problem P, const float *grad_u, float *grad_f,
     cp = (float *)(w + U.ckpt + (size_t)c * (8 * k + 1) * pl);
     // replay the segment, keeping every state (same launch configuration as the forward
     // pass): each iteration reads state j from its slots and writes state j + 1 to the next
-    for (int j = 0; j + 1 < n; j++) {
+    // (on chip in one launch where there is a kernel that keeps the states on their way)
+    bool replayed = false, ok = false;
+    ResidentPlan L;
+    ResidentArgs T;
+    const sl_status rs = resident_prepare(P, n - 1, P->ucfg, P->uA, &ok, &L, &T);
+    if (rs != SL_OK) return rs;
+    if (ok && resident_keeps(P->piece, P->add, L, T.G)) {
+      T.u = uslot(1);
+      T.up = uslot(0);
+      T.s = sslot(1);
+      T.sp = sslot(0);
+      T.v = yv(0);
+      T.z = yz(0);
+      T.q = yq(0);
+      T.p = yp(0);
+      T.ku = useq + (size_t)k * ps;   // state j: u in slot j + 1
+      T.ks = sseq + (size_t)k * ps;
+      T.ky = (float *)yseq;
+      T.kstep = (long long)k * ps;
+      T.ystep = (long long)(yslot / sizeof(float));
+      T.uo = uslot(n);
+      T.upo = uslot(n - 1);
+      T.so = sslot(n);
+      T.spo = sslot(n - 1);
+      T.vo = yv(n - 1);
+      T.zo = yz(n - 1);
+      T.qo = yq(n - 1);
+      T.po = yp(n - 1);
+      const sl_status ls = resident_launch(P, L, T, &replayed);
+      if (ls != SL_OK) return ls;
+    }
+    for (int j = 0; j + 1 < n && !replayed; j++) {
       IterPtrs<float> R = iter_ptrs_f(P);
       R.u = uslot(j + 1);
       R.up = uslot(j);

@@ -124,6 +124,10 @@ struct ResidentArgs {
   // if not NULL: v, z, q and p as they were before the last iteration (p like po), for the residuals
   void *vsave, *zsave, *psave;
   float *qsave;
+  // if not NULL: every state before the last is kept, state i (after i iterations) in
+  // ku + i kstep, ks + i kstep (u, s) and ky + i ystep (v, z, q, p_x, p_y planes)
+  float *ku, *ks, *ky;
+  long long kstep, ystep;
   const float *fn, *wadd, *cost;
   const float4 *tau;
   const unsigned *sinfo;
@@ -146,6 +150,7 @@ struct ResidentPlan {
 };
 // a plan for the problem with G label groups on `cus` compute units; false if it does not fit
 bool resident_plan(int piece, bool add, int H, int W, int k, int G, int qmax, int cus, ResidentPlan *out);
+bool resident_keeps(int piece, bool add, const ResidentPlan &L, int G);   // is there a kernel that keeps states?
 size_t resident_rim_bytes(const ResidentPlan &L, int k);
 size_t resident_exchange_bytes(int piece, bool add, int H, int W, int k, int qmax);   // 0 if no plan fits
 hipError_t launch_resident(int piece, bool add, const ResidentPlan &L, const ResidentArgs &R, hipStream_t st);

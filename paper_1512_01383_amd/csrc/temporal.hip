@@ -191,13 +191,15 @@ constexpr int kMaxBlocks = 256;              // compute units of the chip: the e
 constexpr size_t kOneBlock = 82 * 1024;      // LDS of more than half a compute unit: one block on each
 constexpr size_t kMaxLds = 160 * 1024 - 16 * SLI_MAXK - 64;   // less the kernels' fixed tables
 
-const void *kernel_for(int piece, bool add, int ch, int lg, int rp, int phys, int *ph) {
+const void *kernel_for(int piece, bool add, int ch, int lg, int rp, int phys, int *ph, bool keep = false) {
   using resident::kernel_of;
   if (piece == SLI_TRUNC)
-    return add ? kernel_of<SLI_TRUNC, true>(ch, lg, rp, phys, ph) : kernel_of<SLI_TRUNC, false>(ch, lg, rp, phys, ph);
+    return add ? kernel_of<SLI_TRUNC, true>(ch, lg, rp, phys, ph, keep)
+               : kernel_of<SLI_TRUNC, false>(ch, lg, rp, phys, ph, keep);
   if (piece == SLI_QUAD)
-    return add ? kernel_of<SLI_QUAD, true>(ch, lg, rp, phys, ph) : kernel_of<SLI_QUAD, false>(ch, lg, rp, phys, ph);
-  return kernel_of<SLI_SAMPLED, false>(ch, lg, rp, phys, ph);
+    return add ? kernel_of<SLI_QUAD, true>(ch, lg, rp, phys, ph, keep)
+               : kernel_of<SLI_QUAD, false>(ch, lg, rp, phys, ph, keep);
+  return kernel_of<SLI_SAMPLED, false>(ch, lg, rp, phys, ph, keep);
 }
 
 // fewest wavefronts on top of each other (of rp rows each; two at least: a row is at one rim
@@ -243,6 +245,12 @@ bool resident_plan(int piece, bool add, int H, int W, int k, int G, int qmax, in
   return false;
 }
 
+bool resident_keeps(int piece, bool add, const ResidentPlan &L, int G) {
+  int plain = 0, keep = 0;   // (the LDS layout goes by the label groups that a kernel is made for)
+  return kernel_for(piece, add, L.ch, L.lg, L.rp, G / L.lg, &plain) &&
+         kernel_for(piece, add, L.ch, L.lg, L.rp, G / L.lg, &keep, true) && plain == keep;
+}
+
 // two slots of every tile's rim words (128 + twice its rows, per label)
 size_t resident_rim_bytes(const ResidentPlan &L, int k) {
   return (size_t)2 * L.blocks * k * (128 + 2 * L.th * L.rp) * 8;
@@ -263,7 +271,7 @@ size_t resident_exchange_bytes(int piece, bool add, int H, int W, int k, int qma
 
 hipError_t launch_resident(int piece, bool add, const ResidentPlan &L, const ResidentArgs &R, hipStream_t st) {
   int ph = 0;
-  const void *f = kernel_for(piece, add, L.ch, L.lg, L.rp, R.G / L.lg, &ph);
+  const void *f = kernel_for(piece, add, L.ch, L.lg, L.rp, R.G / L.lg, &ph, R.ku != nullptr);
   if (!f) return hipErrorInvalidValue;
   void *args[] = {const_cast<ResidentArgs *>(&R)};
   return hipLaunchCooperativeKernel(f, dim3(L.blocks), dim3(L.threads), args, (unsigned)L.lds, st);

@@ -57,3 +57,26 @@ def test_first_rows_match_the_oracle(orc, H, L, add):
         a, b = got.double().cpu().numpy()[..., :ROWS, :], ref[..., :ROWS, :]
         assert np.linalg.norm(a - b) <= 1e-3 * np.linalg.norm(b)
         assert np.abs(a - b).max() <= 1e-2 * np.abs(b).max()
+
+
+@pytest.mark.parametrize("add", [True, False])
+@pytest.mark.parametrize("data,H,Wd,L", [("trunc", 37, 130, 5), ("trunc", 64, 65, 8), ("trunc", 41, 70, 12),
+                                         ("trunc", 33, 64, 16), ("phase", 49, 100, 9), ("trunc", 40, 90, 24)])
+def test_replay_on_chip_equals_replay_by_single_launches(data, H, Wd, L, add):
+    """Segments of 12 iterations are replayed on chip (chunks of one to four labels; six: by single
+    launches), segments of four by single launches: the gradients have the same bits."""
+    wl = W.phase_unwrapping(H=H, W=Wd, L=L, seed=31) if data == "phase" else W.truncated_quadratic(L=L, H=H, W=Wd, seed=31)
+    if add and data == "trunc":
+        wl.tau = wl.gamma.copy()
+        wl.samples = np.random.default_rng(32).normal(0, 0.02, (L, H, Wd)).astype(np.float32)
+    out = []
+    for every in (12, 4):
+        p = S.Problem.from_workload(wl)
+        p.unrolled_forward(27, every)
+        _, u = p.read_u()
+        gf, gl, gw = p.unrolled_backward(2.0 * u)
+        out.append((gf, gl, gw))
+        torch.cuda.synchronize()
+        p.close()
+    assert torch.equal(out[0][0], out[1][0]) and out[0][1] == out[1][1]
+    assert (out[0][2] is None and out[1][2] is None) or torch.equal(out[0][2], out[1][2])
