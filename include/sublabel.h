@@ -146,7 +146,15 @@ sl_status sl_create(const sl_problem_desc *desc, void *dev_workspace, size_t byt
 /* Enqueue `iters` (>= 0) primal-dual iterations (Sec. 4): one fused kernel per iteration
  * performs the dual ascent on (v, z, q, p) at the over-relaxed primal point, the
  * projections onto the scaled epigraphs of rho_i^* and onto the l2 balls of K, and the
- * primal descent on (u, s). Asynchronous. */
+ * primal descent on (u, s). Asynchronous.
+ *
+ * A problem whose state fits the registers and LDS of the GPU runs 8 iterations and more in
+ * one cooperative launch (the same iterates, bit for bit), here and in every call that
+ * iterates, unless the stream is being captured. Its tiles wait for each other; should a wait
+ * last some 30 seconds (something keeps part of the launch off the GPU for so long), the launch ends
+ * without it and the iteration state is lost: sl_read_u and sl_save_state then write NaN, and
+ * sl_energy, sl_run_to_gap, sl_residuals, sl_unrolled_backward and sl_solve_static return
+ * SL_ERR_DEVICE, until sl_load_state or sl_autotune sets a new state. */
 sl_status sl_run(sl_problem p, int32_t iters);
 
 /* Run in chunks of check_every iterations until the certified relative gap is

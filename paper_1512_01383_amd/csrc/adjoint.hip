@@ -703,7 +703,7 @@ __global__ void k_adj_finish(const float *cbar, const float *wbar, int nw, float
 }
 
 // fixed-order double sum (one block): reproducible bit for bit
-__global__ __launch_bounds__(1024) void k_sum_double(const double *a, long long n, double *out) {
+__global__ __launch_bounds__(1024) void k_sum_double(const double *a, long long n, double *out, const unsigned *err) {
   __shared__ double sh[1024];
   double acc = 0.0;
   for (long long j = threadIdx.x; j < n; j += 1024) acc += a[j];
@@ -713,7 +713,10 @@ __global__ __launch_bounds__(1024) void k_sum_double(const double *a, long long 
     if ((int)threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = sh[0];
+  if (threadIdx.x == 0) {
+    out[0] = sh[0];
+    out[1] = *err;
+  }
 }
 
 }  // namespace
@@ -801,7 +804,7 @@ hipError_t launch_adj_finish(const float *cbar, const float *wbar, int nw, float
   return hipGetLastError();
 }
 
-hipError_t launch_sum_double(const double *a, long long n, double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_sum_double, dim3(1), dim3(1024), 0, st, a, n, out);
+hipError_t launch_sum_double(const double *a, long long n, double *out, const unsigned *err, hipStream_t st) {
+  hipLaunchKernelGGL(k_sum_double, dim3(1), dim3(1024), 0, st, a, n, out, err);
   return hipGetLastError();
 }

@@ -558,8 +558,10 @@ __device__ __forceinline__ void mon_final_body(const double *part1, const double
   }
   if (threadIdx.x == 0) out[q] = red[0];
 }
-__global__ __launch_bounds__(MB) void monitor_final(const double *part1, const double *part2, int nb, double *out) {
+__global__ __launch_bounds__(MB) void monitor_final(const double *part1, const double *part2, int nb, double *out,
+                                                    const unsigned *err) {
   mon_final_body(part1, part2, nb, out, blockIdx.x);
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[7] = *err;
 }
 
 // A check of one problem: the certificate's pixel terms and the residuals of the interval's
@@ -576,8 +578,9 @@ __global__ __launch_bounds__(MB) void k_check_pixel(IterArgs A, MonArgs D, MonPt
     residuals_body<DT>(R, A, b - nbm, (int)gridDim.x - nbm);
 }
 __global__ __launch_bounds__(MB) void k_check_final(const double *part1, const double *part2, int nbm, double *mon,
-                                                    const double *rpart, int nbr, double *res) {
+                                                    const unsigned *err, const double *rpart, int nbr, double *res) {
   const int q = (int)blockIdx.x;
+  if (q == 0 && threadIdx.x == 0) mon[7] = *err;
   if (q < 7)
     mon_final_body(part1, part2, nbm, mon, q);
   else
@@ -756,17 +759,18 @@ __global__ void k_straddle_info(const float *fn, const float *f_orig, unsigned *
   sinfod[x] = infod;
 }
 
-__global__ void k_readout(const float *u, float *ulift, float *uout, IterArgs A, MonArgs D) {
+__global__ void k_readout(const float *u, float *ulift, float *uout, IterArgs A, MonArgs D, const unsigned *err) {
+  const bool lost = *err != 0;
   const long long N = (long long)A.H * A.W;
   long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= N) return;
   double t = D.gam[0];
   for (int i = 0; i < A.k; i++) {
-    float ui = u[i * A.ps + x];
+    float ui = lost ? __builtin_nanf("") : u[i * A.ps + x];
     if (ulift) ulift[i * N + x] = ui;
     t += D.h[i] * fmin(fmax((double)ui, 0.0), 1.0);
   }
-  if (uout) uout[x] = (float)(D.shift + D.scale * t);
+  if (uout) uout[x] = lost ? __builtin_nanf("") : (float)(D.shift + D.scale * t);
 }
 
 struct PackArgs {
@@ -774,13 +778,15 @@ struct PackArgs {
   int bf16[8 * SLI_MAXK + 1];
 };
 
-__global__ void k_pack(PackArgs P, int np, long long N, long long ps, float *dst, int unpack) {
+__global__ void k_pack(PackArgs P, int np, long long N, long long ps, float *dst, int unpack, unsigned *err) {
+  const bool lost = !unpack && *err != 0;
   long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= N) return;
+  if (unpack && x == 0) *err = 0;
   for (int q = 0; q < np; q++) {
     if (!unpack) {
-      dst[q * N + x] = P.bf16[q] ? ldv((const uint16_t *)P.planes[q], x)
-                                 : ((const float *)P.planes[q])[x];
+      const float val = P.bf16[q] ? ldv((const uint16_t *)P.planes[q], x) : ((const float *)P.planes[q])[x];
+      dst[q * N + x] = lost ? __builtin_nanf("") : val;
     } else {
       float val = dst[q * N + x];
       if (P.bf16[q])
@@ -811,7 +817,7 @@ hipError_t launch_monitor(int piece, bool add, const IterArgs &A, const MonArgs 
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(monitor_tv, dim3(nb), dim3(MB), 0, st, A, D, M);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(monitor_final, dim3(7), dim3(MB), 0, st, M.part1, M.part2, nb, M.final_);
+  hipLaunchKernelGGL(monitor_final, dim3(7), dim3(MB), 0, st, M.part1, M.part2, nb, M.final_, M.err);
   if (nb_out) *nb_out = nb;
   return hipGetLastError();
 }
@@ -831,7 +837,7 @@ hipError_t launch_check(int piece, bool add, const IterArgs &A, const MonArgs &D
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(monitor_tv, dim3(nbm), dim3(MB), 0, st, A, D, M);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_check_final, dim3(7 + 4), dim3(MB), 0, st, M.part1, M.part2, nbm, M.final_,
+  hipLaunchKernelGGL(k_check_final, dim3(7 + 4), dim3(MB), 0, st, M.part1, M.part2, nbm, M.final_, M.err,
                      (const double *)R.part, nbr, res);
   return hipGetLastError();
 }
@@ -905,9 +911,9 @@ hipError_t launch_straddle_info(const float *fn, const float *f_orig, unsigned *
 }
 
 hipError_t launch_readout(const float *u, float *ulift, float *uout, const IterArgs &A,
-                          const MonArgs &D, hipStream_t st) {
+                          const MonArgs &D, const unsigned *err, hipStream_t st) {
   long long N = (long long)A.H * A.W;
-  hipLaunchKernelGGL(k_readout, dim3(nblk(N, 256)), dim3(256), 0, st, u, ulift, uout, A, D);
+  hipLaunchKernelGGL(k_readout, dim3(nblk(N, 256)), dim3(256), 0, st, u, ulift, uout, A, D, err);
   return hipGetLastError();
 }
 
@@ -920,13 +926,13 @@ hipError_t launch_widen_bf16(const uint16_t *src, float *dst, size_t n, hipStrea
 }
 
 hipError_t launch_pack_state(const void *const *planes, const int *bf16, int np, long long N,
-                             long long ps, float *dst, int unpack, hipStream_t st) {
+                             long long ps, float *dst, int unpack, unsigned *err, hipStream_t st) {
   (void)ps;
   PackArgs P;
   for (int q = 0; q < np; q++) {
     P.planes[q] = planes[q];
     P.bf16[q] = bf16[q];
   }
-  hipLaunchKernelGGL(k_pack, dim3(nblk(N, 256)), dim3(256), 0, st, P, np, N, ps, dst, unpack);
+  hipLaunchKernelGGL(k_pack, dim3(nblk(N, 256)), dim3(256), 0, st, P, np, N, ps, dst, unpack, err);
   return hipGetLastError();
 }

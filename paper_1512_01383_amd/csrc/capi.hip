@@ -274,15 +274,18 @@ struct sl_problem_ {
   int nb_mon = 0;   // capacity of the monitor's partial-sum regions, in blocks
   float tau_tab[SLI_MAXM][4] = {};   // per sample: position, 1/(1+t^2), 1/(t_m - t_{m-1}), 0
   double taud_host[SLI_MAXM] = {};
-  double fin[SLI_NMON];
+  double fin[SLI_NMON] = {};   // the monitor's sums; [7]: the error word of the on-chip iteration
   // pinned host staging for the small device-to-host copies of the monitor and residual
   // sums (a copy into pageable memory goes through a bounce buffer and costs ~40 us)
   double *pin = nullptr;
   size_t pin_n = 0;
   // allocation-free problems stage those copies in this fixed host array instead
   bool no_alloc = false;
-  // on-chip iteration: whether this problem may use it, and the tag of the next rim word
-  bool resident = false;
+  // on-chip iteration: whether this problem may use it, and the tag of the next rim word; how
+  // often a wave looks for a word (each look is a round trip to memory, about a microsecond: some
+  // 30 s) and whether a launch has been made yet
+  bool resident = false, launched = false;
+  unsigned wait_limit = 1u << 25;
   int cus = 0;
   unsigned rim_tag = 1;
   int qmax = 0;
@@ -371,6 +374,7 @@ struct sl_problem_ {
 
   float *ubuf(int j) { return (float *)(ws + lay.off_u) + (size_t)j * A.k * lay.ps; }
   float *sbuf(int j) { return (float *)(ws + lay.off_s) + (size_t)j * A.k * lay.ps; }
+  unsigned *err_word() { return (unsigned *)(ws + lay.off_flag) + 1; }
   size_t esz() const { return bf16 ? 2 : 4; }
   char *pbuf(int j) { return ws + lay.off_p + (size_t)j * 2 * A.k * lay.ps * esz(); }
 };
@@ -564,7 +568,8 @@ sl_status resident_prepare(sl_problem_ *P, int iters, int cfg, const IterArgs &A
   R.tau = (const float4 *)(P->ws + P->lay.off_tau);
   R.sinfo = (const unsigned *)(P->ws + P->lay.off_sinfo);
   R.ex = (unsigned long long *)rim;
-  R.err = (unsigned *)(P->ws + P->lay.off_flag) + 1;
+  R.err = P->err_word();
+  R.limit = P->wait_limit;
   R.ps = A.ps;
   R.H = A.H;
   R.W = A.W;
@@ -603,6 +608,7 @@ sl_status resident_launch(sl_problem_ *P, const ResidentPlan &L, const ResidentA
   }
   if (e != hipSuccess) return hip_fail(e, "on-chip iterations launch");
   P->rim_tag += (unsigned)R.iters + 1u;
+  P->launched = true;
   *done = true;
   return SL_OK;
 }
@@ -725,6 +731,7 @@ MonPtrs monitor_ptrs(sl_problem_ *P) {
   M.part1 = (double *)(P->ws + P->lay.off_part1);
   M.part2 = (double *)(P->ws + P->lay.off_part2);
   M.final_ = mon_out(P);
+  M.err = P->err_word();
   M.bf16 = P->bf16;
   return M;
 }
@@ -844,8 +851,17 @@ sl_status batch_copy_tables(sl_problem_ *P, CopyBatch *B) {
   return s;
 }
 
+// An on-chip run gave up a wait (something kept part of its blocks off the chip): its state is
+// lost until another is loaded, and this problem stays off the chip from now on.
+sl_status gave_up(sl_problem_ *P) {
+  P->resident = false;
+  return fail(SL_ERR_DEVICE, "an on-chip run gave up waiting for a neighbouring tile: the iteration state is lost "
+              "(load a state or create the problem anew)");
+}
+
 // the report from the monitor sums in P->fin (best-so-far bounds updated)
 sl_status monitor_finish(sl_problem_ *P, sl_report *out) {
+  if (P->fin[7] != 0.0) return gave_up(P);
   const double lam = P->lam;
   const double pr = P->fin[0] + lam * P->fin[4];
   const double pg = P->fin[1] + lam * P->fin[5];
@@ -893,7 +909,8 @@ sl_status pinned(sl_problem_ *P, size_t n, double **out) {
 
 // The sums of a check land in the pinned buffer itself (the kernels write it directly: a copy
 // of 56 bytes costs as much as a small kernel); without one (allocation-free problems) they
-// go to the workspace and are copied. stage[0 .. 6]: monitor, stage[8 .. 11]: residuals.
+// go to the workspace and are copied. stage[0 .. 6]: monitor, stage[7]: the error word of the
+// on-chip iteration, stage[8 .. 11]: residuals.
 constexpr size_t kStage = 16;
 
 sl_status monitor(sl_problem_ *P, sl_report *out) {
@@ -904,9 +921,9 @@ sl_status monitor(sl_problem_ *P, sl_report *out) {
   if (!P->no_alloc) M.final_ = stage;
   HIPCHK(launch_monitor(P->piece, P->add, P->A, P->D, M, P->st, nullptr), "monitor launch");
   if (P->no_alloc)
-    HIPCHK(hipMemcpyAsync(stage, mon_out(P), 7 * sizeof(double), hipMemcpyDeviceToHost, P->st), "monitor copy");
+    HIPCHK(hipMemcpyAsync(stage, mon_out(P), 8 * sizeof(double), hipMemcpyDeviceToHost, P->st), "monitor copy");
   HIPCHK(hipStreamSynchronize(P->st), "monitor sync");
-  memcpy(P->fin, stage, 7 * sizeof(double));
+  memcpy(P->fin, stage, 8 * sizeof(double));
   return monitor_finish(P, out);
 }
 
@@ -1013,6 +1030,7 @@ sl_status reset_state(sl_problem_ *P) {
     return SL_OK;
   }
   HIPCHK(launch_fill_zero(P->ws + P->lay.state_lo, P->lay.state_hi - P->lay.state_lo, P->st), "reset");
+  HIPCHK(launch_fill_zero(P->ws + P->lay.off_flag, 16, P->st), "reset");
   P->iters = 0;
   P->have_best = false;
   reset_finishing(P);
@@ -1414,9 +1432,14 @@ sl_status residuals_of_last(sl_problem_ *P, double *res) {
   sl_status s = residuals_enqueue(P);
   if (s != SL_OK) return s;
   double *h = nullptr;
-  if ((s = pinned(P, 4, &h)) != SL_OK) return s;
+  if ((s = pinned(P, kStage, &h)) != SL_OK) return s;
+  unsigned *const lost = (unsigned *)(h + 4);
+  *lost = 0;
   HIPCHK(hipMemcpyAsync(h, res_out(P), 4 * sizeof(double), hipMemcpyDeviceToHost, P->st), "residual copy");
+  if (P->launched)
+    HIPCHK(hipMemcpyAsync(lost, P->err_word(), sizeof(unsigned), hipMemcpyDeviceToHost, P->st), "error word");
   HIPCHK(hipStreamSynchronize(P->st), "residual sync");
+  if (*lost) return gave_up(P);
   for (int j = 0; j < 4; j++) res[j] = h[j];
   return SL_OK;
 }
@@ -1448,11 +1471,11 @@ sl_status iterate_and_check(sl_problem_ *P, int iters, double *res) {
   double *const rout = P->no_alloc ? res_out(P) : stage + 8;
   HIPCHK(launch_check(P->piece, P->add, P->A, P->D, M, residual_ptrs(P), rout, P->st), "check");
   if (P->no_alloc) {
-    HIPCHK(hipMemcpyAsync(stage, mon_out(P), 7 * sizeof(double), hipMemcpyDeviceToHost, P->st), "check copy");
+    HIPCHK(hipMemcpyAsync(stage, mon_out(P), 8 * sizeof(double), hipMemcpyDeviceToHost, P->st), "check copy");
     HIPCHK(hipMemcpyAsync(stage + 8, rout, 4 * sizeof(double), hipMemcpyDeviceToHost, P->st), "check copy");
   }
   HIPCHK(hipStreamSynchronize(P->st), "check sync");
-  memcpy(P->fin, stage, 7 * sizeof(double));
+  memcpy(P->fin, stage, 8 * sizeof(double));
   for (int j = 0; j < 4; j++) res[j] = stage[8 + j];
   return SL_OK;
 }
@@ -1515,7 +1538,7 @@ ULayout unrolled_layout(const sl_problem_ *P, int K, int C) {
   U.cbar = take(pl);
   U.wbar = take(P->add ? (size_t)(k + 1) * pl : 0);
   U.lbar = take((size_t)P->lay.ps * 8);
-  U.lsum = take(8);
+  U.lsum = take(16);
   U.total = o;
   return U;
 }
@@ -1764,7 +1787,7 @@ static sl_status single_run_to_gap(sl_problem_ *P, double rel_gap, int32_t max_i
       // the check interval's last iteration measures the residuals that steer the balance
       double res[4];
       if ((s = iterate_and_check(P, chunk, res)) != SL_OK) return s;
-      adapt_balance(P, res);
+      if (P->fin[7] == 0.0) adapt_balance(P, res);   // (else monitor_finish has the error)
       n += chunk;
       s = monitor_finish(P, &r);
     } else {
@@ -1796,7 +1819,7 @@ sl_status sl_read_u(sl_problem P, float *ulift, float *u) {
   if (!P) return fail(SL_ERR_INVALID_ARG, "handle is NULL");
   if (P->is_batch) return fail(SL_ERR_INVALID_ARG, "batch handle: use sl_batch_read_u");
   if (!ulift && !u) return SL_OK;
-  HIPCHK(launch_readout(P->ubuf(P->iu), ulift, u, P->A, P->D, P->st), "readout");
+  HIPCHK(launch_readout(P->ubuf(P->iu), ulift, u, P->A, P->D, P->err_word(), P->st), "readout");
   return SL_OK;
 }
 
@@ -1822,7 +1845,7 @@ static sl_status pack(sl_problem P, void *buf, size_t bytes, int unpack) {
   std::vector<int> bf;
   state_planes(P, pl, bf);
   HIPCHK(launch_pack_state(pl.data(), bf.data(), (int)pl.size(), P->lay.N, P->lay.ps, (float *)buf,
-                           unpack, P->st),
+                           unpack, P->err_word(), P->st),
          "state pack");
   return SL_OK;
 }
@@ -2267,11 +2290,12 @@ sl_status sl_unrolled_backward(sl_problem P, const float *grad_u, float *grad_f,
                            P->st),
          "gradients");
   double *lsum = (double *)(w + U.lsum);
-  HIPCHK(launch_sum_double(Q.lbar, N, lsum, P->st), "lambda reduction");
-  double hl = 0.0;
-  HIPCHK(hipMemcpyAsync(&hl, lsum, sizeof(double), hipMemcpyDeviceToHost, P->st), "lambda copy");
+  HIPCHK(launch_sum_double(Q.lbar, N, lsum, P->err_word(), P->st), "lambda reduction");
+  double hl[2] = {};   // the sum, the error word of the on-chip iteration
+  HIPCHK(hipMemcpyAsync(hl, lsum, sizeof hl, hipMemcpyDeviceToHost, P->st), "lambda copy");
   HIPCHK(hipStreamSynchronize(P->st), "backward sync");
-  if (grad_lambda) *grad_lambda = hl * P->scale;
+  if (hl[1] != 0.0) return gave_up(P);
+  if (grad_lambda) *grad_lambda = hl[0] * P->scale;
   return SL_OK;
 }
 
@@ -2454,6 +2478,9 @@ sl_status sl_stereo_costs(const float *left, const float *right, int32_t H, int3
   return SL_OK;
 }
 
+// For tests of a wait that is given up (no part of the C-ABI).
+void slx_set_wait_limit(sl_problem P, unsigned looks) { P->wait_limit = looks; }
+
 void sl_destroy(sl_problem P) {
   if (!P) return;
   (void)hipStreamSynchronize(P->st);
@@ -2482,9 +2509,14 @@ sl_status sl_solve_static(const sl_problem_desc *desc, double rel_gap, int32_t m
     s = enqueue_iters(&P, max_iters);
   if (s == SL_OK && (u_lifted_dev || u_dev)) s = sl_read_u(&P, u_lifted_dev, u_dev);
   if (s == SL_OK && report) s = monitor(&P, report);
+  unsigned lost = 0;
+  hipError_t e = hipSuccess;
+  if (s == SL_OK && P.launched) e = hipMemcpyAsync(&lost, P.err_word(), sizeof lost, hipMemcpyDeviceToHost, P.st);
   // the next call on this device reuses the array: finish here
-  const hipError_t e = hipStreamSynchronize(P.st);
+  const hipError_t es = hipStreamSynchronize(P.st);
+  if (e == hipSuccess) e = es;
   if (s == SL_OK && e != hipSuccess) s = hip_fail(e, "static solve sync");
+  if (s == SL_OK && lost) s = gave_up(&P);
   return s;
 }
 

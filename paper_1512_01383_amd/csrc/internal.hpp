@@ -112,7 +112,9 @@ hipError_t launch_pdhg_band(int piece, const BandPtrs &P, const IterArgs &A, hip
 
 // Many iterations per launch with the state on chip (resident.hpp). The state at iteration n
 // is read from u .. q and the state at n + iters written to uo .. qo, which may be the same
-// planes; ex holds two slots of rim words per tile, err is raised if a wait was given up.
+// planes; ex holds two slots of rim words per tile. A wave that has looked for a
+// neighbour's word in vain more than `limit` times gives up and raises err: the state is lost
+// then, and whatever reads it (read-out, saving, sums of a check) looks at err.
 struct ResidentLabel {
   float g0, g1, h, ih, sig, taus, ig0, ig1;
 };
@@ -134,6 +136,7 @@ struct ResidentArgs {
   unsigned long long *ex;
   unsigned *err;
   long long ps;
+  unsigned limit;
   int H, W, k, G, TH, iters;
   unsigned tag;           // of the state at n; tag + i names iteration n + i
   float sig_p, sig_q, tau_c, lam, a, ia, nu, del, per, iper;
@@ -174,7 +177,8 @@ struct MonPtrs {
   const double *taud;     // normalised sample positions in double (SAMPLED)
   const unsigned *sinfod; // straddling intervals with FP64 hull ranges (TRUNC_QUAD)
   double *mon_u, *mon_b;
-  double *part1, *part2, *final_;
+  double *part1, *part2, *final_;   // final_: 7 sums, then (checks of one problem) the error word
+  const unsigned *err;              // of the on-chip iteration
   int bf16;
 };
 
@@ -196,10 +200,12 @@ hipError_t launch_widen_bf16(const uint16_t *src, float *dst, size_t n, hipStrea
 // (sinfod: the same in FP64 from f_orig for the monitor, whose hull is that of the exact samples)
 hipError_t launch_straddle_info(const float *fn, const float *f_orig, unsigned *sinfo, unsigned *sinfod,
                                 const IterArgs &A, const MonArgs &D, hipStream_t st);
+// (both write NaN where the error word of the on-chip iteration is raised; unpacking, which
+// replaces the whole state, lowers it)
 hipError_t launch_readout(const float *u, float *ulift, float *uout, const IterArgs &A,
-                          const MonArgs &D, hipStream_t st);
+                          const MonArgs &D, const unsigned *err, hipStream_t st);
 hipError_t launch_pack_state(const void *const *planes, const int *bf16, int nplanes,
-                             long long N, long long ps, float *dst, int unpack,
+                             long long N, long long ps, float *dst, int unpack, unsigned *err,
                              hipStream_t st);
 
 // Reverse pass (adjoint.hip): one state of the unrolled forward pass (read only), the
@@ -225,7 +231,8 @@ hipError_t launch_adj_readout(const float *gu, const float *u, float *ub, const 
                               hipStream_t st);
 hipError_t launch_adj_finish(const float *cbar, const float *wbar, int nw, float *gf, float *gw, long long N,
                              long long ps, float iscale, hipStream_t st);
-hipError_t launch_sum_double(const double *a, long long n, double *out, hipStream_t st);
+// out[0]: the sum, out[1]: the word at err
+hipError_t launch_sum_double(const double *a, long long n, double *out, const unsigned *err, hipStream_t st);
 // n0, n1: float counts, multiples of 4 (whole planes), 16-byte aligned
 // copies of whole planes: n floats each, a multiple of 4
 struct PlaneCopies {

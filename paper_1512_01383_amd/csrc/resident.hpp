@@ -29,8 +29,11 @@
 // arithmetic) comes first and hides the exchange; the neighbours' values enter with p.
 //
 // The wait ends because all blocks are on the chip at the same time (a cooperative launch)
-// and each publishes before it waits; should it last longer than kWaitTicks all the same,
-// the wave stops waiting for the rest of the launch and raises the error word.
+// and each publishes before it waits; should a wave have looked R.limit times in vain all the
+// same, it raises the error word and stops waiting for the rest of the launch. (Looks, not
+// time, so that a wave does not give up over time in which it was off the chip itself.) What
+// it and its neighbours compute from then on is void: every reader of the state looks at the
+// error word.
 //
 // Labels are walked, summed and rounded as the one-pass kernel does with G label groups
 // (G = LG groups per thread times the groups of the block), so the iterates are bitwise
@@ -41,8 +44,6 @@
 #include "internal.hpp"
 
 namespace resident {
-
-constexpr unsigned long long kWaitTicks = 2000000000ull;   // 20 s of the 100 MHz clock
 
 __device__ __forceinline__ float rdlane(float x, int l) {
   return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), l));
@@ -228,6 +229,8 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
     if (RP == 1 && CH >= 7) in_turn();
   };
 
+  // the error word when the launch began (a scalar load; it is looked at once)
+  const unsigned lost = *(const __attribute__((address_space(4))) unsigned *)R.err;
   // ---- the state
   float u[E], s[E], v[E], z[E], px[E], q[RP], fc[RP], lam = uniform(R.lam);
   // a dual's value in plane i of `base` at byte offset off of a float plane
@@ -370,6 +373,10 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
   const int nc = LIST ? __builtin_amdgcn_readfirstlane(lcount[1]) : 0;
   const int bc = (nc + 63) / 64, batches = bc + (nq + 63) / 64, waves = (int)blockDim.x >> 6;
   publish(R.tag);
+  // Nothing to do for a state that an earlier launch has lost: no second wait of that length.
+  // (Here and not earlier: spills ahead of the loop are put where this block starts, with all
+  // lanes on, and not at the end of publish's divergent part.)
+  if (lost != 0u) return;
 
   // a dual into plane i of `base`, at byte offset off of a float plane
   auto std_ = [&](void *base, int i, unsigned off, float val) {
@@ -456,7 +463,7 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
     };
     if (EARLY) request(0);
     float pl = 0.f;   // new px left of the tile, label i0 + lane
-    u64 t0 = 0;
+    unsigned looks = 0;   // in vain
     auto wait = [&](int b0) {
       if (!EARLY || b0 > 0) request(b0);
       while (true) {
@@ -466,13 +473,12 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
           for (int j = 0; j < HB; j++) wrong |= (unsigned)(hw[j] >> 32) ^ tag;
         }
         if (dead || !__any(wrong != 0u)) break;
-        const u64 now = wall_clock64();
-        if (t0 == 0) t0 = now;
-        if (now - t0 > kWaitTicks) {
+        if (looks++ == R.limit) {
           dead = true;
           *R.err = 1u;
         }
-        request(b0);
+        __builtin_amdgcn_s_sleep(1);   // 64 clocks between looks: without, up to 1 % slower (256x256, L = 20)
+        request(b0);   // (also after giving up: a second way out of this loop costs spills)
       }
     };
     auto p_update = [&]() {
@@ -812,7 +818,7 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
   stop = R.iters;
   }
 
-  // ---- the state back to memory (after a wait that was given up: no state, but NaN)
+  // ---- the state back to memory (of a wave that gave up: NaN)
   if (dead) {
 #pragma unroll
     for (int e = 0; e < E; e++) u[e] = __builtin_nanf("");
