@@ -192,7 +192,9 @@ sl_status sl_load_state(sl_problem p, const void *dev_src, size_t bytes);
  * are captured once in a hipGraph and replayed. sl_run and sl_run_to_gap accept the
  * batch handle; sl_run_to_gap checks every problem each check interval (rounded up to a
  * multiple of 6) and drops problems that reached the gap from the work list (their state
- * is kept). The workspace holds every problem's workspace plus the work tables.
+ * is kept). The workspace holds every problem's workspace plus the work tables; the problems'
+ * tile rims, which a batch does not use, may be left out of it (a refused call's message gives
+ * the bytes needed without them).
  * sl_energy / sl_read_u / sl_save_state on a batch handle return SL_ERR_INVALID_ARG /
  * SL_ERR_UNSUPPORTED: use the sl_batch_* calls. Each problem's iterates are bitwise those
  * of the same problem solved alone with the same tiling. */

@@ -1862,18 +1862,29 @@ sl_status sl_load_state(sl_problem P, const void *src, size_t bytes) {
   return s;
 }
 
-sl_status sl_batch_workspace_size(const sl_problem_desc *descs, int32_t n, size_t *bytes) {
+}  // extern "C"
+
+// bytes of a batch's workspace: what its members use (base: without the rim words, since they
+// advance together, launch by launch), or every member's own sl_workspace_size, plus the tables
+static sl_status batch_bytes(const sl_problem_desc *descs, int32_t n, size_t *bytes, bool base) {
   if (!descs || n < 1 || !bytes) return fail(SL_ERR_INVALID_ARG, "need descs, n >= 1 and bytes");
   size_t total = 0;
   std::vector<int> maxtiles;
   for (int i = 0; i < n; i++) {
     sl_status s = validate(&descs[i]);
     if (s != SL_OK) return fail(s, "instance %d: %s", i, g_err.c_str());
-    total += align256(make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W)).total);
+    const Layout lay = make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W));
+    total += align256(base ? lay.base : lay.total);
     maxtiles.push_back(max_tiles(descs[i].H, descs[i].W));
   }
   *bytes = total + batch_table_bytes(maxtiles, n);
   return SL_OK;
+}
+
+extern "C" {
+
+sl_status sl_batch_workspace_size(const sl_problem_desc *descs, int32_t n, size_t *bytes) {
+  return batch_bytes(descs, n, bytes, false);
 }
 
 sl_status sl_batch_create(const sl_problem_desc *descs, int32_t n, void *ws, size_t bytes,
@@ -1881,7 +1892,7 @@ sl_status sl_batch_create(const sl_problem_desc *descs, int32_t n, void *ws, siz
   if (!out) return fail(SL_ERR_INVALID_ARG, "out is NULL");
   *out = nullptr;
   size_t need = 0;
-  sl_status s = sl_batch_workspace_size(descs, n, &need);
+  sl_status s = batch_bytes(descs, n, &need, true);
   if (s != SL_OK) return s;
   if (!ws || ((uintptr_t)ws & 255)) return fail(SL_ERR_WORKSPACE, "workspace NULL or not 256-byte aligned");
   if (bytes < need) return fail(SL_ERR_WORKSPACE, "workspace of %zu bytes is smaller than the %zu needed", bytes, need);
@@ -1903,9 +1914,8 @@ sl_status sl_batch_create(const sl_problem_desc *descs, int32_t n, void *ws, siz
   std::vector<int> maxtiles;
   for (int i = 0; i < n; i++) {
     const Layout lay = make_layout(&descs[i], monitor_blocks_max((long long)descs[i].H * descs[i].W));
-    const size_t sz = align256(lay.total);
+    const size_t sz = align256(lay.base);
     sl_problem q = nullptr;
-    // (without the rim words: a batch's members advance together, launch by launch)
     s = create_impl(&descs[i], base + off, lay.base, stream, &q);
     if (s != SL_OK) {
       delete B;
