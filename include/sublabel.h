@@ -213,7 +213,9 @@ sl_status sl_set_graphs(sl_problem p, int32_t enable);
  * (each tiling keeps its faster time, so the costlier first iterations from a fresh state
  * do not count against the tiling timed first), keeps the fastest (a later tiling only if
  * it is faster by more than 2 %), then resets the iteration state (and the adaptive step
- * balance) to its initial value (call it before iterating). With a cache file (may be NULL) a tiling measured
+ * balance) to its initial value (call it before iterating). For a problem that fits the GPU
+ * (see sl_run) the on-chip launch of each number of label groups is timed, with 8 iterations
+ * or more, and the faster tiling of those groups kept. With a cache file (may be NULL) a tiling measured
  * before for the same device, kernel variant (data term, storage, TV kind), label count and
  * size bucket (power of two of the pixel count) is reused without timing, and new
  * measurements are appended as lines "key|tiling". The chosen (label_groups, tile_rows,

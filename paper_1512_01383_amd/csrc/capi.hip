@@ -539,16 +539,20 @@ sl_status band_quad(sl_problem_ *P) {
 // saves 3 us on the smallest problems and more on larger ones.
 constexpr int kResidentMin = 8;
 
+// The problem's plan on the chip with the label groups of configuration cfg; false if it has none.
+bool resident_fits(const sl_problem_ *P, int cfg, ResidentPlan *L) {
+  return P->resident &&
+         resident_plan(P->piece, P->add, P->A.H, P->A.W, P->A.k, kIterCfg[cfg][0], P->qmax, P->cus, L) &&
+         resident_rim_bytes(*L, P->A.k) <= P->lay.rim;
+}
+
 // May `iters` iterations with the label groups of configuration cfg run on chip now (the problem
 // fits, the stream is not being captured)? Then its plan and the launch's arguments but for the state.
 sl_status resident_prepare(sl_problem_ *P, int iters, int cfg, const IterArgs &A, bool *ok, ResidentPlan *plan,
                            ResidentArgs *args) {
   *ok = false;
   ResidentPlan &L = *plan;
-  if (!P->resident || iters < kResidentMin ||
-      !resident_plan(P->piece, P->add, A.H, A.W, A.k, kIterCfg[cfg][0], P->qmax, P->cus, &L) ||
-      resident_rim_bytes(L, A.k) > P->lay.rim)
-    return SL_OK;
+  if (iters < kResidentMin || !resident_fits(P, cfg, &L)) return SL_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(P->st, &cap) != hipSuccess) {
     (void)hipGetLastError();
@@ -2039,6 +2043,12 @@ sl_status sl_set_graphs(sl_problem P, int32_t enable) {
 // Time `iters` iterations with every tiling that fits, keep the fastest, and reset the
 // iteration state to its initial value. With a cache file, a tiling measured before for
 // the same device, kernel variant, label count and size bucket is reused.
+//
+// What a run of a single problem uses is timed: where the label groups of a tiling have a plan
+// on the chip, that launch. Tilings of the same groups are the same on the chip; among them the
+// one-launch-per-iteration kernel decides, which runs of fewer iterations use. Ranked by the
+// latter alone, groups without a plan could win (256x256, L = 20: 7.9 us an iteration on chip
+// with four groups, the only ones with a plan there, 17.8 off it).
 sl_status sl_autotune(sl_problem P, int32_t iters, const char *cache_path, int32_t *label_groups,
                       int32_t *tile_rows, int32_t *tile_cols) {
   if (!P || iters < 1) return fail(SL_ERR_INVALID_ARG, "need a handle and iters >= 1");
@@ -2058,6 +2068,15 @@ sl_status sl_autotune(sl_problem P, int32_t iters, const char *cache_path, int32
   for (const sl_problem_ *q : P->sub) tv |= q->A.aniso;
   snprintf(key, sizeof key, "%s piece=%d add=%d bf16=%d tv=%d batch=%d k=%d n2=%d", prop.gcnArchName, P->piece,
            (int)P->add, (int)P->bf16, tv, (int)P->is_batch, P->is_batch ? P->kmax : P->A.k, nb);
+  // (with a shadow workspace set, runs do not go by the tiling's label groups)
+  const bool chip = P->resident && !P->band_ws;
+  auto on_chip = [&](int c) {
+    ResidentPlan L;
+    return chip && cfg_fits(P, c) && resident_fits(P, c, &L);
+  };
+  bool any_chip = false;
+  for (int c = 0; c < SLI_NCFG; c++) any_chip |= on_chip(c);
+  if (any_chip) strncat(key, " chip=1", sizeof key - strlen(key) - 1);   // other entries were ranked off the chip
   int best = -1;
   if (cache_path) {
     FILE *fp = fopen(cache_path, "r");
@@ -2069,7 +2088,7 @@ sl_status sl_autotune(sl_problem P, int32_t iters, const char *cache_path, int32
         *bar = 0;
         if (strcmp(line, key) == 0) {
           int c = atoi(bar + 1);
-          if (c >= 0 && c < SLI_NCFG && cfg_fits(P, c)) best = c;
+          if (c >= 0 && c < SLI_NCFG && cfg_fits(P, c) && (!any_chip || on_chip(c))) best = c;
         }
       }
       fclose(fp);
@@ -2109,14 +2128,57 @@ sl_status sl_autotune(sl_problem P, int32_t iters, const char *cache_path, int32
         t[c] = std::min(t[c], ms);
       }
     }
+    // the same on the chip, once per number of label groups
+    float tc[SLI_NCFG];
+    for (int c = 0; c < SLI_NCFG; c++) {
+      tc[c] = 1e30f;
+      if (!on_chip(c)) continue;
+      int d = 0;
+      while (d < c && !(tc[d] < 1e30f && kIterCfg[d][0] == kIterCfg[c][0])) d++;
+      if (d < c) {
+        tc[c] = tc[d];
+        continue;
+      }
+      P->cfg = c;
+      const int n = std::max(iters, kResidentMin);
+      for (int round = 0; round < 3; round++) {   // the first: the kernel's first launch
+        HIPCHK(hipEventRecord(e0, P->st), "event record");
+        const sl_status s = enqueue_iters(P, n, kSameBits);
+        if (s != SL_OK) return s;
+        HIPCHK(hipEventRecord(e1, P->st), "event record");
+        HIPCHK(hipEventSynchronize(e1), "event sync");
+        float ms = 0.f;
+        HIPCHK(hipEventElapsedTime(&ms, e0, e1), "elapsed");
+        if (round > 0) tc[c] = std::min(tc[c], ms * (float)iters / (float)n);
+      }
+    }
+    if (P->launched) {
+      unsigned lost = 0;
+      HIPCHK(hipMemcpyAsync(&lost, P->err_word(), sizeof lost, hipMemcpyDeviceToHost, P->st), "error word");
+      HIPCHK(hipStreamSynchronize(P->st), "error word");
+      if (lost) {
+        P->resident = false;
+        for (float &x : tc) x = 1e30f;
+      }
+    }
     // a later configuration must be faster by more than the run-to-run spread (2 %):
     // near-equal timings keep the earlier one, so the choice is stable between runs
-    float best_ms = 1e30f;
-    for (int c = 0; c < SLI_NCFG; c++) {
-      if (t[c] < best_ms * 0.98f) {
-        best_ms = t[c];
-        best = c;
+    auto fastest = [&](auto time_of) {
+      float best_ms = 1e30f;
+      int at = -1;
+      for (int c = 0; c < SLI_NCFG; c++) {
+        const float ms = time_of(c);
+        if (ms < best_ms * 0.98f) {
+          best_ms = ms;
+          at = c;
+        }
       }
+      return at;
+    };
+    best = fastest([&](int c) { return tc[c] < 1e30f ? tc[c] : t[c]; });
+    if (best >= 0 && tc[best] < 1e30f) {
+      const int groups = kIterCfg[best][0];
+      best = fastest([&](int c) { return kIterCfg[c][0] == groups ? t[c] : 1e30f; });
     }
     if (best < 0) return fail(SL_ERR_UNSUPPORTED, "no tiling fits");
     if (cache_path) {
