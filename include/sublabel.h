@@ -317,8 +317,11 @@ sl_status sl_set_storage(sl_problem p, int32_t i, sl_storage storage);
  * of four iterations as two passes that each read the state once and write it once,
  * through a shadow copy of the state in a caller-owned workspace. The iterates are
  * bitwise those of the one-pass kernel with one label group (launch configurations with
- * G = 1); other configurations differ in rounding only. Iterations of the unrolled
- * forward pass and of sl_autotune keep the one-pass kernel.
+ * G = 1); other configurations differ in rounding only. Runs of 24 iterations and more of a
+ * problem that fits the GPU (see sl_run) go on chip with one label group instead, which gives
+ * the same iterates sooner; the passes pay for larger images, and without this setting such a
+ * problem may use more label groups on chip. The unrolled forward pass and sl_autotune do not
+ * use the passes.
  * sl_temporal_workspace_size: bytes of that workspace ((8k+1) planes of 4 H*W bytes,
  *   rounded as the state's planes are).
  * sl_set_temporal: ws (device, 256-byte aligned, owned by the caller and kept valid while

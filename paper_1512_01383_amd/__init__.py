@@ -292,7 +292,8 @@ class Problem:
     def set_temporal(self, on: bool = True):
         """Run groups of four iterations as two two-iteration passes (k <= 3, FP32,
         quadratic or truncated-quadratic data); the shadow workspace is allocated here and
-        kept until set_temporal(False) or close."""
+        kept until set_temporal(False) or close. For images that do not fit the chip: runs of
+        24 iterations and more of one that does go on chip, setting or not."""
         if not on:
             _check(lib().sl_set_temporal(self.h, None, 0))
             self._band_ws = None

@@ -617,15 +617,15 @@ sl_status resident_launch(sl_problem_ *P, const ResidentPlan &L, const ResidentA
   return SL_OK;
 }
 
-// `iters` iterations in one on-chip launch; *done is set if the problem and its stream allow
+// `iters` iterations in one on-chip launch with the label groups of configuration cfg; *done is set if the problem and its stream allow
 // it (a stream that is being captured keeps the plain launches). save: also keep the duals
 // before the last iteration, as save_duals does.
-sl_status resident_run(sl_problem_ *P, int iters, bool *done, bool save = false) {
+sl_status resident_run(sl_problem_ *P, int iters, int cfg, bool *done, bool save = false) {
   *done = false;
   bool ok = false;
   ResidentPlan L;
   ResidentArgs R;
-  sl_status s = resident_prepare(P, iters, P->cfg, P->A, &ok, &L, &R);
+  sl_status s = resident_prepare(P, iters, cfg, P->A, &ok, &L, &R);
   if (s != SL_OK || !ok) return s;
   R.u = P->ubuf(P->iu);
   R.up = P->ubuf((P->iu + 2) % 3);
@@ -659,12 +659,24 @@ sl_status resident_run(sl_problem_ *P, int iters, bool *done, bool save = false)
 }
 
 // How enqueue_iters may run its iterations: one launch per iteration only; on-chip launches
-// too (bitwise the same iterates); or also, with a shadow workspace set, groups of four by
-// the two-iteration kernel (bitwise the iterates of one label group).
+// too (bitwise the same iterates); or also, with a shadow workspace set, groups of four with
+// one label group: by the two-iteration kernel, or on chip (the same iterates, bit for bit).
 enum RunBy { kOnePass, kSameBits, kAny };
+
+// Configuration of one label group, and the iterations from which its on-chip launch beats
+// passes of two iterations: with the launch's cost they are even at 21 for ROF 64 x 64 (2.46 us
+// an iteration in passes, 1.45 on chip and 22 a launch), at 20 for 256 x 256, 10 for
+// 1531 x 2039 (25 and 16.5), 14 for 256 x 256 with 3 quadratic intervals (4.9 and 3.2).
+constexpr int kOneGroup = 0, kBandChip = 24;
 
 sl_status enqueue_iters(sl_problem_ *P, int iters, RunBy by = kAny) {
   if (by == kAny && P->band_ws) {
+    bool done = false;
+    if (iters >= kBandChip) {
+      const sl_status s = resident_run(P, iters / 4 * 4, kOneGroup, &done);
+      if (s != SL_OK) return s;
+      if (done) iters %= 4;
+    }
     for (; iters >= 4; iters -= 4) {
       const sl_status s = band_quad(P);
       if (s != SL_OK) return s;
@@ -672,7 +684,7 @@ sl_status enqueue_iters(sl_problem_ *P, int iters, RunBy by = kAny) {
   }
   if (by != kOnePass) {
     bool done = false;
-    const sl_status s = resident_run(P, iters, &done);
+    const sl_status s = resident_run(P, iters, P->cfg, &done);
     if (s != SL_OK || done) return s;
   }
   for (int n = 0; n < iters; n++) {
@@ -1461,7 +1473,7 @@ sl_status iterate_with_residuals(sl_problem_ *P, double *res) {
 // monitor's sums of the state after them in P->fin: one wait for both.
 sl_status iterate_and_check(sl_problem_ *P, int iters, double *res) {
   bool done = false;
-  sl_status s = P->band_ws ? SL_OK : resident_run(P, iters, &done, true);
+  sl_status s = P->band_ws ? SL_OK : resident_run(P, iters, P->cfg, &done, true);
   if (s == SL_OK && !done) {
     s = enqueue_iters(P, iters - 1);
     if (s == SL_OK) s = save_duals(P);
