@@ -148,8 +148,8 @@ sl_status sl_create(const sl_problem_desc *desc, void *dev_workspace, size_t byt
  * projections onto the scaled epigraphs of rho_i^* and onto the l2 balls of K, and the
  * primal descent on (u, s). Asynchronous.
  *
- * A problem whose state fits the registers and LDS of the GPU runs 8 iterations and more in
- * one cooperative launch (the same iterates, bit for bit), here and in every call that
+ * A problem whose state fits the registers and LDS of the GPU runs 8 iterations and more (16
+ * where its labels and rows per thread are many) in one cooperative launch (the same iterates, bit for bit), here and in every call that
  * iterates, unless the stream is being captured. Its tiles wait for each other; should a wait
  * last some 30 seconds (something keeps part of the launch off the GPU for so long), the launch ends
  * without it and the iteration state is lost: sl_read_u and sl_save_state then write NaN, and
@@ -214,8 +214,8 @@ sl_status sl_set_graphs(sl_problem p, int32_t enable);
  * do not count against the tiling timed first), keeps the fastest (a later tiling only if
  * it is faster by more than 2 %), then resets the iteration state (and the adaptive step
  * balance) to its initial value (call it before iterating). For a problem that fits the GPU
- * (see sl_run) the on-chip launch of each number of label groups is timed, with 8 iterations
- * or more, and the faster tiling of those groups kept. With a cache file (may be NULL) a tiling measured
+ * (see sl_run) the on-chip launch of each number of label groups is timed, with the iterations
+ * it takes at least, and the faster tiling of those groups kept. With a cache file (may be NULL) a tiling measured
  * before for the same device, kernel variant (data term, storage, TV kind), label count and
  * size bucket (power of two of the pixel count) is reused without timing, and new
  * measurements are appended as lines "key|tiling". The chosen (label_groups, tile_rows,

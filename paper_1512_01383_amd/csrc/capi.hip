@@ -534,11 +534,6 @@ sl_status band_quad(sl_problem_ *P) {
   return SL_OK;
 }
 
-// Iterations from which a run is worth an on-chip launch: a cooperative launch costs about
-// 20 us more than a plain one (measured 21.0 against 2.2 us back to back), and an iteration
-// saves 3 us on the smallest problems and more on larger ones.
-constexpr int kResidentMin = 8;
-
 // The problem's plan on the chip with the label groups of configuration cfg; false if it has none.
 bool resident_fits(const sl_problem_ *P, int cfg, ResidentPlan *L) {
   return P->resident &&
@@ -552,7 +547,7 @@ sl_status resident_prepare(sl_problem_ *P, int iters, int cfg, const IterArgs &A
                            ResidentArgs *args) {
   *ok = false;
   ResidentPlan &L = *plan;
-  if (iters < kResidentMin || !resident_fits(P, cfg, &L)) return SL_OK;
+  if (!resident_fits(P, cfg, &L) || iters < resident_least(L, P->bf16)) return SL_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(P->st, &cap) != hipSuccess) {
     (void)hipGetLastError();
@@ -2082,8 +2077,8 @@ sl_status sl_autotune(sl_problem P, int32_t iters, const char *cache_path, int32
            (int)P->add, (int)P->bf16, tv, (int)P->is_batch, P->is_batch ? P->kmax : P->A.k, nb);
   // (with a shadow workspace set, runs do not go by the tiling's label groups)
   const bool chip = P->resident && !P->band_ws;
+  ResidentPlan L;
   auto on_chip = [&](int c) {
-    ResidentPlan L;
     return chip && cfg_fits(P, c) && resident_fits(P, c, &L);
   };
   bool any_chip = false;
@@ -2152,7 +2147,7 @@ sl_status sl_autotune(sl_problem P, int32_t iters, const char *cache_path, int32
         continue;
       }
       P->cfg = c;
-      const int n = std::max(iters, kResidentMin);
+      const int n = std::max(iters, resident_least(L, P->bf16));
       for (int round = 0; round < 3; round++) {   // the first: the kernel's first launch
         HIPCHK(hipEventRecord(e0, P->st), "event record");
         const sl_status s = enqueue_iters(P, n, kSameBits);

@@ -153,6 +153,7 @@ struct ResidentPlan {
 };
 // a plan for the problem with G label groups on `cus` compute units; false if it does not fit
 bool resident_plan(int piece, bool add, int H, int W, int k, int G, int qmax, int cus, ResidentPlan *out);
+int resident_least(const ResidentPlan &L, bool bf16);   // iterations from which a launch pays
 bool resident_keeps(int piece, bool add, const ResidentPlan &L, int G);   // is there a kernel that keeps states?
 size_t resident_rim_bytes(const ResidentPlan &L, int k);
 size_t resident_exchange_bytes(int piece, bool add, int H, int W, int k, int qmax);   // 0 if no plan fits

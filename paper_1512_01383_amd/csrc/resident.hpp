@@ -848,11 +848,13 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
   }
 }
 
-// What is built: every chunk length up to 10 labels per thread, with a wavefront per label
-// group in blocks of up to 4 groups; the chunks of two or four label groups that a thread takes
+// What is built: chunks of up to 8 labels per thread, with a wavefront per label group in blocks
+// of up to 4 groups, and of 9 in blocks of one; the chunks of two or four label groups that a thread takes
 // together when the image has too many tiles for a wavefront per group; for long chunks (whose
 // LDS is scarce) blocks of one group of threads apart from those of several; several rows per
-// thread for few labels. Returns the kernel for `phys` groups of threads and its PH.
+// thread for few labels. Not built, because one launch per iteration is as fast: two rows of 6
+// quadratic labels (1501x192: 19.6 us on chip, 19.1 off it) and two groups of 5 quadratic labels
+// with additive values (701x256: 21.8 and 21.7, with bf16 duals 22.4 and 20.7). Returns the kernel for `phys` groups of threads and its PH.
 template <int PIECE, bool ADD>
 inline const void *kernel_of(int ch, int lg, int rp, int phys, int *ph, bool keep) {
   if (keep) {   // the shapes of the images that are differentiated through
@@ -887,7 +889,7 @@ inline const void *kernel_of(int ch, int lg, int rp, int phys, int *ph, bool kee
   SLI_RES(4, 2, 1, 2)
   SLI_RES(6, 2, 1, 2)
   SLI_RES(8, 2, 1, 1)
-  SLI_RES(10, 2, 1, 1)
+  if constexpr (!(PIECE == SLI_QUAD && ADD)) SLI_RES(10, 2, 1, 1)
   SLI_RES(8, 2, 1, 2)
   SLI_RES(4, 4, 1, 1)
   SLI_RES(8, 4, 1, 1)
@@ -910,7 +912,6 @@ inline const void *kernel_of(int ch, int lg, int rp, int phys, int *ph, bool kee
     SLI_RES(4, 1, 2, 1)
     SLI_RES(4, 1, 3, 1)
     SLI_RES(5, 1, 2, 1)
-    SLI_RES(6, 1, 2, 1)
   }
 #undef SLI_RES
   return nullptr;

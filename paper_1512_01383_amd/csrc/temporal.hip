@@ -245,6 +245,17 @@ bool resident_plan(int piece, bool add, int H, int W, int k, int G, int qmax, in
   return false;
 }
 
+// A cooperative launch costs about 20 us more than a plain one (measured 21.0 against 2.2 us back
+// to back), and the state's way in and out 3 to 30; an iteration saves 3 us on the smallest
+// problems and more on larger ones: even at 3 to 8 iterations. Threads of many elements with 3
+// labels or more to a row (whose registers spill) save less. Quadratics of 1399x322 with 4
+// intervals, 12 elements: 21.3 us an iteration off the chip, 16.8 on it and 46 a launch, even at
+// 10, with bf16 duals at 15; 1399x540 with 3, 12 elements: at 7 and 15; 1501x192 with 5, 10
+// elements: at 7 and 9; samples 701x193 with 9, 10 elements: at 8 and 12.
+int resident_least(const ResidentPlan &L, bool bf16) {
+  return L.ch >= 3 && L.ch * L.rp >= (bf16 ? 10 : 12) ? 16 : 8;
+}
+
 bool resident_keeps(int piece, bool add, const ResidentPlan &L, int G) {
   int plain = 0, keep = 0;   // (the LDS layout goes by the label groups that a kernel is made for)
   return kernel_for(piece, add, L.ch, L.lg, L.rp, G / L.lg, &plain) &&
