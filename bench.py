@@ -12,7 +12,8 @@ average duration of the batched iteration kernel against its algorithmic bytes (
 the time for every member to reach a 1e-3 certified relative gap (bf16 with the float
 finishing phase, against the members solved one after another and the batch in float),
 the FP64 CPU oracle timed on a bounded sample of the same members (baseline, not the
-target), and single-instance kernel timings (256^2 cache-resident, 2048^2 in HBM).
+target), and single-instance kernel timings (256^2 cache-resident, 2048^2 in HBM; and the time per
+iteration of long runs, which keep the 256^2 instance on chip).
 Other workloads: tq (one truncated-quadratic instance), stereo, phase, diff, labels.
 """
 from __future__ import annotations
@@ -30,6 +31,10 @@ sys.path.insert(0, ROOT)
 HBM_PEAK_GBS = 8000.0
 CHECK_EVERY = 50
 CHECK_BATCH = 48      # check interval of batched solves (a multiple of the 6-iteration period)
+# Longest runs that are one launch per iteration for every problem (longer ones of a problem
+# that fits the GPU keep its state on chip and move none of the bytes counted here), and
+# longest that keep the two-iteration passes where those are switched on
+SINGLE_RUN, PASSES_RUN = 7, 20
 KERNEL_SOURCES = ("paper_1512_01383_amd/csrc/pdhg_iter.hip", "paper_1512_01383_amd/csrc/device_math.hpp",
                   "paper_1512_01383_amd/csrc/internal.hpp")
 
@@ -159,15 +164,10 @@ def main():
     ms_per_step = dt / args.steps * 1e3
     value = N * k * CHECK_EVERY * args.steps / dt
 
-    # dominant kernel: HIP events around a run of fused iterations on the library's stream
-    ev0 = torch.cuda.Event(enable_timing=True)
-    ev1 = torch.cuda.Event(enable_timing=True)
-    g.run(20)
-    ev0.record(stream)
-    g.run(args.kernel_iters)
-    ev1.record(stream)
-    ev1.synchronize()
-    kern_ms = ev0.elapsed_time(ev1) / args.kernel_iters
+    # the kernel of one launch per iteration, which moves the bytes counted here; and what an
+    # iteration of a long run takes (on chip, where the problem fits)
+    kern_ms = ms_per_iteration(g, args.kernel_iters, SINGLE_RUN)
+    run_ms = ms_per_iteration(g, args.kernel_iters, args.kernel_iters)
     bpp = algorithmic_bytes_per_pixel(k, wl.rho, wl.M, args.storage == "bf16", False)
     bytes_per_launch = bpp * N
     achieved = bytes_per_launch / (kern_ms * 1e-3) / 1e9
@@ -288,7 +288,7 @@ def main():
                                  if args.workload == "tq" else
                                  measured_traffic(f"stereo{wl.W}x{wl.H}_L{wl.L}_{args.storage}", tiling=g.get_tiling())
                                  if args.workload == "stereo" else None),
-                     "kernel": "pdhg_iter_kernel", "kernel_ms": kern_ms,
+                     "kernel": "pdhg_iter_kernel", "kernel_ms": kern_ms, "long_run_ms_per_iteration": run_ms,
                      "algorithmic_bytes_per_launch": bytes_per_launch,
                      "kernel_hash": kernel_hash(), "tiling": list(g.get_tiling())},
         "cpu_baseline": cpu,
@@ -529,24 +529,36 @@ def host_cores() -> int:
     return len(os.sched_getaffinity(0)) if hasattr(os, "sched_getaffinity") else os.cpu_count()
 
 
-def single_kernel_timing(S, wl, storage, dev, iters=200):
-    """HIP-event average duration of the fused iteration kernel of one instance (the
-    library's stream, after a short warm-up) against its algorithmic bytes."""
+def ms_per_iteration(g, iters, run):
+    """HIP-event time per iteration of `iters` iterations in runs of `run` (on the library's
+    stream, after a short warm-up)."""
     import torch
-    g = S.Problem.from_workload(wl, storage=storage, device=dev)
-    g.run(20)
+    for _ in range(3):
+        g.run(run if run < 50 else 20)
     ev0 = torch.cuda.Event(enable_timing=True)
     ev1 = torch.cuda.Event(enable_timing=True)
+    n = max(1, iters // run)
     ev0.record(g.stream)
-    g.run(iters)
+    for _ in range(n):
+        g.run(run)
     ev1.record(g.stream)
     ev1.synchronize()
-    ms = ev0.elapsed_time(ev1) / iters
+    return ev0.elapsed_time(ev1) / (n * run)
+
+
+def single_kernel_timing(S, wl, storage, dev, iters=210):
+    """Time per iteration of the kernel of one launch per iteration on one instance against its
+    algorithmic bytes, and of long runs, which keep the state of an instance that fits the GPU
+    on chip and move none of those bytes."""
+    g = S.Problem.from_workload(wl, storage=storage, device=dev)
+    ms = ms_per_iteration(g, iters, SINGLE_RUN)
+    run_ms = ms_per_iteration(g, iters, iters)
     tiling = g.get_tiling()
     g.close()
     nbytes = algorithmic_bytes_per_pixel(wl.k, wl.rho, wl.M, storage == "bf16", False) * wl.H * wl.W
     return {"H": wl.H, "W": wl.W, "L": wl.L, "storage": storage, "kernel_ms": ms,
-            "pixel_label_iter_per_s": wl.H * wl.W * wl.k / (ms * 1e-3),
+            "long_run_ms_per_iteration": run_ms,
+            "pixel_label_iter_per_s": wl.H * wl.W * wl.k / (run_ms * 1e-3),
             "algorithmic_bytes_per_launch": nbytes, "achieved_GBs": nbytes / (ms * 1e-3) / 1e9,
             "frac": nbytes / (ms * 1e-3) / 1e9 / HBM_PEAK_GBS, "tiling": list(tiling)}
 
@@ -893,7 +905,8 @@ def bench_temporal(args):
     """Temporal blocking (two iterations per pass over the state, k <= 3) against the
     one-pass kernel on the same problems: HIP-event time per iteration of each (the
     one-pass kernel in its automatic and in its one-group configuration, the two-iteration
-    passes in groups of four iterations), the one-pass algorithmic bytes per iteration and
+    passes in groups of four iterations; in runs short enough that neither goes on chip, and for
+    the images that fit there the time per iteration of long runs), the one-pass algorithmic bytes per iteration and
     the bytes a two-iteration pass moves (reported apart: temporal blocking changes the
     accounting). Value: pixel-label-iterations/s of the two-iteration path on the largest
     instance."""
@@ -902,16 +915,6 @@ def bench_temporal(args):
     import workloads as W
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
-
-    def timed(g, iters):
-        g.run(8)
-        e0 = torch.cuda.Event(enable_timing=True)
-        e1 = torch.cuda.Event(enable_timing=True)
-        e0.record(g.stream)
-        g.run(iters)
-        e1.record(g.stream)
-        e1.synchronize()
-        return e0.elapsed_time(e1) / iters
 
     cases = [("rof_64_L2", W.rof(), 2000),
              ("rof_2048_L2", W.rof(H=2048, W=2048, seed=11), 200),
@@ -923,18 +926,19 @@ def bench_temporal(args):
     rows = {}
     for name, wl, iters in cases:
         g = S.Problem.from_workload(wl, device=dev)
-        auto_ms = timed(g, iters)
+        auto_ms = ms_per_iteration(g, iters, SINGLE_RUN)
+        long_ms = ms_per_iteration(g, iters, iters)
         auto_tiling = list(g.get_tiling())
         g.set_tiling(1, 4, 64)
-        one_ms = timed(g, iters)
+        one_ms = ms_per_iteration(g, iters, SINGLE_RUN)
         g.set_temporal(True)
-        band_ms = timed(g, iters)
+        band_ms = ms_per_iteration(g, iters, PASSES_RUN)
         g.close()
         nb1 = algorithmic_bytes_per_pixel(wl.k, wl.rho, wl.M, False, False) * wl.H * wl.W
         nbb = band_bytes_per_pass(wl)
         rows[name] = {"H": wl.H, "W": wl.W, "L": wl.L, "iters": iters,
                       "one_pass_ms": auto_ms, "one_pass_tiling": auto_tiling, "one_group_ms": one_ms,
-                      "two_iteration_ms": band_ms, "speedup": auto_ms / band_ms,
+                      "two_iteration_ms": band_ms, "speedup": auto_ms / band_ms, "long_run_ms": long_ms,
                       "one_pass_bytes_per_iteration": nb1, "two_iteration_bytes_per_pass": nbb,
                       "one_pass_GBs": nb1 / (auto_ms * 1e-3) / 1e9,
                       "two_iteration_GBs": nbb / (2 * band_ms * 1e-3) / 1e9}
