@@ -715,7 +715,7 @@ __global__ __launch_bounds__(1024) void k_sum_double(const double *a, long long 
   }
   if (threadIdx.x == 0) {
     out[0] = sh[0];
-    out[1] = *err;
+    out[1] = scalar_word(err);
   }
 }
 

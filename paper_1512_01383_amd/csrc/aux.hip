@@ -561,7 +561,7 @@ __device__ __forceinline__ void mon_final_body(const double *part1, const double
 __global__ __launch_bounds__(MB) void monitor_final(const double *part1, const double *part2, int nb, double *out,
                                                     const unsigned *err) {
   mon_final_body(part1, part2, nb, out, blockIdx.x);
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[7] = *err;
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[7] = scalar_word(err);
 }
 
 // A check of one problem: the certificate's pixel terms and the residuals of the interval's
@@ -580,7 +580,7 @@ __global__ __launch_bounds__(MB) void k_check_pixel(IterArgs A, MonArgs D, MonPt
 __global__ __launch_bounds__(MB) void k_check_final(const double *part1, const double *part2, int nbm, double *mon,
                                                     const unsigned *err, const double *rpart, int nbr, double *res) {
   const int q = (int)blockIdx.x;
-  if (q == 0 && threadIdx.x == 0) mon[7] = *err;
+  if (q == 0 && threadIdx.x == 0) mon[7] = scalar_word(err);
   if (q < 7)
     mon_final_body(part1, part2, nbm, mon, q);
   else
@@ -760,14 +760,14 @@ __global__ void k_straddle_info(const float *fn, const float *f_orig, unsigned *
 }
 
 __global__ void k_readout(const float *u, float *ulift, float *uout, IterArgs A, MonArgs D, const unsigned *err) {
-  const bool lost = *err != 0;
+  const bool lost = scalar_word(err) != 0;
   const long long N = (long long)A.H * A.W;
   long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= N) return;
   double t = D.gam[0];
   for (int i = 0; i < A.k; i++) {
-    float ui = lost ? __builtin_nanf("") : u[i * A.ps + x];
-    if (ulift) ulift[i * N + x] = ui;
+    float ui = u[i * A.ps + x];
+    if (ulift) ulift[i * N + x] = lost ? __builtin_nanf("") : ui;
     t += D.h[i] * fmin(fmax((double)ui, 0.0), 1.0);
   }
   if (uout) uout[x] = lost ? __builtin_nanf("") : (float)(D.shift + D.scale * t);
@@ -778,13 +778,14 @@ struct PackArgs {
   int bf16[8 * SLI_MAXK + 1];
 };
 
-__global__ void k_pack(PackArgs P, int np, long long N, long long ps, float *dst, int unpack, unsigned *err) {
-  const bool lost = !unpack && *err != 0;
+template <bool UNPACK>
+__global__ void k_pack(PackArgs P, int np, long long N, float *dst, unsigned *err) {
+  const bool lost = !UNPACK && scalar_word(err) != 0;
   long long x = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (x >= N) return;
-  if (unpack && x == 0) *err = 0;
+  if (UNPACK && x == 0) *err = 0;
   for (int q = 0; q < np; q++) {
-    if (!unpack) {
+    if (!UNPACK) {
       const float val = P.bf16[q] ? ldv((const uint16_t *)P.planes[q], x) : ((const float *)P.planes[q])[x];
       dst[q * N + x] = lost ? __builtin_nanf("") : val;
     } else {
@@ -933,6 +934,6 @@ hipError_t launch_pack_state(const void *const *planes, const int *bf16, int np,
     P.planes[q] = planes[q];
     P.bf16[q] = bf16[q];
   }
-  hipLaunchKernelGGL(k_pack, dim3(nblk(N, 256)), dim3(256), 0, st, P, np, N, ps, dst, unpack, err);
+  hipLaunchKernelGGL(unpack ? k_pack<true> : k_pack<false>, dim3(nblk(N, 256)), dim3(256), 0, st, P, np, N, dst, err);
   return hipGetLastError();
 }

@@ -159,7 +159,7 @@ Layout make_layout(const sl_problem_desc *d, int nb_mon) {
     A.W = d->W;
     L.off_rpart = take((size_t)residual_blocks(A) * 32);
   }
-  L.off_rfin = take(32);
+  L.off_rfin = take(40);
   L.base = o;
   L.rim = resident_exchange_bytes(piece_of(d->rho), !sampled && d->samples, d->H, d->W, k, band_most(d));
   L.off_rim = take(L.rim);
@@ -235,6 +235,9 @@ __global__ void k_nonfinite(const float *a, long long n, unsigned *flag) {
 
 }  // namespace
 
+// no tag is left (or none was given out yet): the next launch starts over on cleared rim words
+constexpr unsigned kNoTag = 0xFFFFFFFFu;
+
 struct sl_problem_ {
   sl_problem_desc d;
   int piece = 0;
@@ -287,7 +290,7 @@ struct sl_problem_ {
   bool resident = false, launched = false;
   unsigned wait_limit = 1u << 25;
   int cus = 0;
-  unsigned rim_tag = 1;
+  unsigned rim_tag = kNoTag;
   int qmax = 0;
   // two iterations per pass (temporal blocking): the caller's shadow state, 8k+1 planes
   char *band_ws = nullptr;
@@ -547,7 +550,7 @@ sl_status resident_prepare(sl_problem_ *P, int iters, int cfg, const IterArgs &A
                            ResidentArgs *args) {
   *ok = false;
   ResidentPlan &L = *plan;
-  if (!resident_fits(P, cfg, &L) || iters < resident_least(L, P->bf16)) return SL_OK;
+  if (iters < kResidentLeast || !resident_fits(P, cfg, &L) || iters < resident_least(L, P->bf16)) return SL_OK;
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(P->st, &cap) != hipSuccess) {
     (void)hipGetLastError();
@@ -555,7 +558,7 @@ sl_status resident_prepare(sl_problem_ *P, int iters, int cfg, const IterArgs &A
   }
   if (cap != hipStreamCaptureStatusNone) return SL_OK;
   char *rim = P->ws + P->lay.off_rim;
-  if (P->rim_tag > 0xFFFFFFFFu - (unsigned)iters - 2u) {   // tags start over on cleared words
+  if (P->rim_tag > kNoTag - (unsigned)iters - 2u) {
     HIPCHK(launch_fill_zero(rim, P->lay.rim, P->st), "rim words");
     P->rim_tag = 1;
   }
@@ -1195,7 +1198,6 @@ sl_status batch_enqueue(sl_problem_ *P, int iters) {
 }
 
 sl_status save_duals(sl_problem_ *P);
-sl_status residuals_enqueue(sl_problem_ *P, const IterArgs *A_dev = nullptr);
 void adapt_balance(sl_problem_ *P, const double *res);
 
 // Run `enqueue(stream)` (work of every active member at a check) from graph slot g: captured
@@ -1409,8 +1411,8 @@ double *res_out(sl_problem_ *P) {
   return P->fin_dev ? P->fin_dev + 8 : (double *)(P->ws + P->lay.off_rfin);
 }
 
-// residual norms of the iteration that followed save_duals, enqueued (4 sums at res_out(P):
-// primal, dual, |K^T y|, |K x|); residuals_of_last also waits for them
+// residual norms of the iteration that followed save_duals (4 sums: primal, dual, |K^T y|,
+// |K x|); residuals_of_last waits for them
 ResPtrs residual_ptrs(sl_problem_ *P) {
   const int k = P->A.k;
   const size_t pdb = (size_t)P->lay.ps * P->esz();
@@ -1433,24 +1435,16 @@ ResPtrs residual_ptrs(sl_problem_ *P) {
   return R;
 }
 
-sl_status residuals_enqueue(sl_problem_ *P, const IterArgs *A_dev) {
-  const ResPtrs R = residual_ptrs(P);
-  HIPCHK(launch_residuals(P->bf16, R, P->A, res_out(P), P->st, A_dev), "residuals");
-  return SL_OK;
-}
-
 sl_status residuals_of_last(sl_problem_ *P, double *res) {
-  sl_status s = residuals_enqueue(P);
-  if (s != SL_OK) return s;
   double *h = nullptr;
-  if ((s = pinned(P, kStage, &h)) != SL_OK) return s;
-  unsigned *const lost = (unsigned *)(h + 4);
-  *lost = 0;
-  HIPCHK(hipMemcpyAsync(h, res_out(P), 4 * sizeof(double), hipMemcpyDeviceToHost, P->st), "residual copy");
-  if (P->launched)
-    HIPCHK(hipMemcpyAsync(lost, P->err_word(), sizeof(unsigned), hipMemcpyDeviceToHost, P->st), "error word");
+  sl_status s = pinned(P, kStage, &h);
+  if (s != SL_OK) return s;
+  double *const out = P->no_alloc ? res_out(P) : h;
+  HIPCHK(launch_residuals(P->bf16, residual_ptrs(P), P->A, out, P->err_word(), P->st), "residuals");
+  if (P->no_alloc)
+    HIPCHK(hipMemcpyAsync(h, out, 5 * sizeof(double), hipMemcpyDeviceToHost, P->st), "residual copy");
   HIPCHK(hipStreamSynchronize(P->st), "residual sync");
-  if (*lost) return gave_up(P);
+  if (h[4] != 0.0) return gave_up(P);
   for (int j = 0; j < 4; j++) res[j] = h[j];
   return SL_OK;
 }
@@ -1718,8 +1712,6 @@ static sl_status init_impl(sl_problem_ *P, const sl_problem_desc *desc, void *ws
   // zero state, data planes
   if ((e = launch_fill_zero(P->ws + lay.state_lo, lay.state_hi - lay.state_lo, P->st)) != hipSuccess)
     return hip_fail(e, "zero state");
-  if (P->resident && (e = launch_fill_zero(P->ws + lay.off_rim, lay.rim, P->st)) != hipSuccess)
-    return hip_fail(e, "rim words");
   if (P->piece != SLI_SAMPLED) {
     float fs = (float)P->shift, is = (float)(1.0 / P->scale);
     if ((e = launch_init_fn(desc->f, (float *)(P->ws + lay.off_fn), N, fs, is, P->st)) != hipSuccess)
@@ -2588,9 +2580,10 @@ sl_status sl_solve_static(const sl_problem_desc *desc, double rel_gap, int32_t m
     s = enqueue_iters(&P, max_iters);
   if (s == SL_OK && (u_lifted_dev || u_dev)) s = sl_read_u(&P, u_lifted_dev, u_dev);
   if (s == SL_OK && report) s = monitor(&P, report);
+  // a report, and the last check of a run to a gap, have looked at the error word already
   unsigned lost = 0;
   hipError_t e = hipSuccess;
-  if (s == SL_OK && P.launched) e = hipMemcpyAsync(&lost, P.err_word(), sizeof lost, hipMemcpyDeviceToHost, P.st);
+  if (s == SL_OK && P.launched && !report && !(rel_gap > 0.0)) e = hipMemcpyAsync(&lost, P.err_word(), sizeof lost, hipMemcpyDeviceToHost, P.st);
   // the next call on this device reuses the array: finish here
   const hipError_t es = hipStreamSynchronize(P.st);
   if (e == hipSuccess) e = es;

@@ -52,6 +52,12 @@ __device__ __forceinline__ float ldvb(const uint16_t *base, unsigned off) {
 __device__ __forceinline__ void stvb(float *base, unsigned off, float x) { stb(base, off, x); }
 __device__ __forceinline__ void stvb(uint16_t *base, unsigned off, float x) { stb(base, off, f2bf(x)); }
 
+// A word that no wave of the kernel looks at again, through the scalar cache: it comes with the
+// kernel's arguments instead of ahead of the first vector load's wait.
+__device__ __forceinline__ unsigned scalar_word(const unsigned *p) {
+  return *(const __attribute__((address_space(4))) unsigned *)p;
+}
+
 // Buffer loads / stores through a descriptor of one plane of `bytes` bytes. The hardware
 // range check makes a lane whose byte offset lies at or beyond `bytes` read 0 and write
 // nothing, so lanes outside the image (offset kOOB) and whole steps past the end of a

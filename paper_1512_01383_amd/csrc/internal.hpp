@@ -153,7 +153,9 @@ struct ResidentPlan {
 };
 // a plan for the problem with G label groups on `cus` compute units; false if it does not fit
 bool resident_plan(int piece, bool add, int H, int W, int k, int G, int qmax, int cus, ResidentPlan *out);
-int resident_least(const ResidentPlan &L, bool bf16);   // iterations from which a launch pays
+// iterations from which a launch pays: of any plan, of this one
+constexpr int kResidentLeast = 8;
+int resident_least(const ResidentPlan &L, bool bf16);
 bool resident_keeps(int piece, bool add, const ResidentPlan &L, int G);   // is there a kernel that keeps states?
 size_t resident_rim_bytes(const ResidentPlan &L, int k);
 size_t resident_exchange_bytes(int piece, bool add, int H, int W, int k, int qmax);   // 0 if no plan fits
@@ -253,6 +255,7 @@ struct ResPtrs {
   double *part;
 };
 int residual_blocks(const IterArgs &A);
+// out[0 .. 3]: the sums, out[4]: the word at err
 // A_dev (may be NULL): read the parameters from this device copy of A instead of the argument
-hipError_t launch_residuals(bool bf16, const ResPtrs &R, const IterArgs &A, double *out, hipStream_t st,
-                            const IterArgs *A_dev = nullptr);
+hipError_t launch_residuals(bool bf16, const ResPtrs &R, const IterArgs &A, double *out, const unsigned *err,
+                            hipStream_t st, const IterArgs *A_dev = nullptr);

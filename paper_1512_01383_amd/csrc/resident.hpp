@@ -229,8 +229,7 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
     if (RP == 1 && CH >= 7) in_turn();
   };
 
-  // the error word when the launch began (a scalar load; it is looked at once)
-  const unsigned lost = *(const __attribute__((address_space(4))) unsigned *)R.err;
+  const unsigned lost = scalar_word(R.err);   // the error word when the launch began
   // ---- the state
   float u[E], s[E], v[E], z[E], px[E], q[RP], fc[RP], lam = uniform(R.lam);
   // a dual's value in plane i of `base` at byte offset off of a float plane

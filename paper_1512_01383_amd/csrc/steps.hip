@@ -40,7 +40,8 @@ __global__ __launch_bounds__(RB) void k_residuals_batch(const ResPtrs *__restric
   residuals_body<DT>(R[j], A[j], blk, nb);
 }
 
-__global__ __launch_bounds__(RB) void k_sum_quads(const double *part, int nb, double *out) {
+__global__ __launch_bounds__(RB) void k_sum_quads(const double *part, int nb, double *out, const unsigned *err) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) out[4] = scalar_word(err);
   sum_quads_body(part, nb, out, blockIdx.x);
 }
 // grid (4, nl): column blockIdx.x of list entry blockIdx.y
@@ -72,8 +73,8 @@ int residual_blocks(const IterArgs &A) {
   return (int)(nb < 1024 ? nb : 1024);
 }
 
-hipError_t launch_residuals(bool bf16, const ResPtrs &R, const IterArgs &A, double *out, hipStream_t st,
-                            const IterArgs *A_dev) {
+hipError_t launch_residuals(bool bf16, const ResPtrs &R, const IterArgs &A, double *out, const unsigned *err,
+                            hipStream_t st, const IterArgs *A_dev) {
   const int nb = residual_blocks(A);
   if (A_dev) {
     if (bf16)
@@ -85,6 +86,6 @@ hipError_t launch_residuals(bool bf16, const ResPtrs &R, const IterArgs &A, doub
   } else {
     hipLaunchKernelGGL(k_residuals<float>, dim3(nb), dim3(RB), 0, st, R, A);
   }
-  hipLaunchKernelGGL(k_sum_quads, dim3(4), dim3(RB), 0, st, (const double *)R.part, nb, out);
+  hipLaunchKernelGGL(k_sum_quads, dim3(4), dim3(RB), 0, st, (const double *)R.part, nb, out, err);
   return hipGetLastError();
 }

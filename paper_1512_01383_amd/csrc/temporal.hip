@@ -253,7 +253,7 @@ bool resident_plan(int piece, bool add, int H, int W, int k, int G, int qmax, in
 // 10, with bf16 duals at 15; 1399x540 with 3, 12 elements: at 7 and 15; 1501x192 with 5, 10
 // elements: at 7 and 9; samples 701x193 with 9, 10 elements: at 8 and 12.
 int resident_least(const ResidentPlan &L, bool bf16) {
-  return L.ch >= 3 && L.ch * L.rp >= (bf16 ? 10 : 12) ? 16 : 8;
+  return L.ch >= 3 && L.ch * L.rp >= (bf16 ? 10 : 12) ? 16 : kResidentLeast;
 }
 
 bool resident_keeps(int piece, bool add, const ResidentPlan &L, int G) {
