@@ -235,9 +235,6 @@ __global__ void k_nonfinite(const float *a, long long n, unsigned *flag) {
 
 }  // namespace
 
-// no tag is left (or none was given out yet): the next launch starts over on cleared rim words
-constexpr unsigned kNoTag = 0xFFFFFFFFu;
-
 struct sl_problem_ {
   sl_problem_desc d;
   int piece = 0;
@@ -290,7 +287,7 @@ struct sl_problem_ {
   bool resident = false, launched = false;
   unsigned wait_limit = 1u << 25;
   int cus = 0;
-  unsigned rim_tag = kNoTag;
+  unsigned rim_tag = 1;
   int qmax = 0;
   // two iterations per pass (temporal blocking): the caller's shadow state, 8k+1 planes
   char *band_ws = nullptr;
@@ -558,7 +555,7 @@ sl_status resident_prepare(sl_problem_ *P, int iters, int cfg, const IterArgs &A
   }
   if (cap != hipStreamCaptureStatusNone) return SL_OK;
   char *rim = P->ws + P->lay.off_rim;
-  if (P->rim_tag > kNoTag - (unsigned)iters - 2u) {
+  if (P->rim_tag > 0xFFFFFFFFu - (unsigned)iters - 2u) {   // tags start over on cleared words
     HIPCHK(launch_fill_zero(rim, P->lay.rim, P->st), "rim words");
     P->rim_tag = 1;
   }
@@ -1712,6 +1709,10 @@ static sl_status init_impl(sl_problem_ *P, const sl_problem_desc *desc, void *ws
   // zero state, data planes
   if ((e = launch_fill_zero(P->ws + lay.state_lo, lay.state_hi - lay.state_lo, P->st)) != hipSuccess)
     return hip_fail(e, "zero state");
+  // (here, where the launch overlaps the rest of the set-up: ahead of the first on-chip launch it
+  // cost a new problem's first run 10 us)
+  if (P->resident && (e = launch_fill_zero(P->ws + lay.off_rim, lay.rim, P->st)) != hipSuccess)
+    return hip_fail(e, "rim words");
   if (P->piece != SLI_SAMPLED) {
     float fs = (float)P->shift, is = (float)(1.0 / P->scale);
     if ((e = launch_init_fn(desc->f, (float *)(P->ws + lay.off_fn), N, fs, is, P->st)) != hipSuccess)
