@@ -150,7 +150,8 @@ sl_status sl_create(const sl_problem_desc *desc, void *dev_workspace, size_t byt
  *
  * A problem whose state fits the registers and LDS of the GPU runs 8 iterations and more (16
  * where its labels and rows per thread are many) in one cooperative launch (the same iterates, bit for bit), here and in every call that
- * iterates, unless the stream is being captured. Its tiles wait for each other; should a wait
+ * iterates, unless the stream is being captured. The first such launch of a process takes some
+ * 10 ms more, and those of several streams run one after another. Its tiles wait for each other; should a wait
  * last some 30 seconds (something keeps part of the launch off the GPU for so long), the launch ends
  * without it and the iteration state is lost: sl_read_u and sl_save_state then write NaN, and
  * sl_energy, sl_run_to_gap, sl_residuals, sl_unrolled_backward and sl_solve_static return

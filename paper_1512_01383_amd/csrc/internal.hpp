@@ -236,14 +236,14 @@ hipError_t launch_adj_finish(const float *cbar, const float *wbar, int nw, float
                              long long ps, float iscale, hipStream_t st);
 // out[0]: the sum, out[1]: the word at err
 hipError_t launch_sum_double(const double *a, long long n, double *out, const unsigned *err, hipStream_t st);
-// n0, n1: float counts, multiples of 4 (whole planes), 16-byte aligned
-// copies of whole planes: n floats each, a multiple of 4
+// copies of whole planes: n floats each, a multiple of 4, 16-byte aligned
 struct PlaneCopies {
   const void *src[8];
   void *dst[8];
   long long n[8];
 };
 hipError_t launch_plane_copies(const PlaneCopies &C, int segments, hipStream_t st);
+// n0, n1: float counts, multiples of 4 (whole planes), 16-byte aligned
 hipError_t launch_copy2(const float *s0, float *d0, size_t n0, const float *s1, float *d1, size_t n1,
                         hipStream_t st);
 

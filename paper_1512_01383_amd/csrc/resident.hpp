@@ -6,11 +6,20 @@
 // whole launch, every thread CH labels of one pixel, and only the rim of each tile travels
 // between blocks. That takes away the launch, the loads and stores of 14 planes per label
 // and the waits on them. Measured, us per iteration, one launch per iteration -> on chip:
-// ROF 64 x 64, L = 2: 5.0 -> 1.6, 1531 x 2039: 37 -> 19 (12 rows per thread); truncated
-// quadratic 256 x 256, L = 5: 9.1 -> 3.7, L = 20: 17.8 -> 7.9, 353 x 517, L = 10 (anisotropic):
-// 30 -> 16.5; phase 256 x 256, L = 8: 8.5 -> 3.8; stereo 288 x 384, L = 8: 21.5 -> 13.5. What is
-// left is bound by the vector unit (and on the smallest problems by the serial chain of one
-// iteration: 1.1 us of it is the round trip of the rim, measured with no work around it).
+// ROF 64 x 64, L = 2: 5.0 -> 1.5, 1531 x 2039: 37 -> 19 (12 rows per thread); truncated
+// quadratic 256 x 256, L = 5: 9.1 -> 3.3, L = 20: 17.8 -> 7.7, 353 x 517, L = 10 (anisotropic):
+// 30 -> 16; phase 256 x 256, L = 8: 8.5 -> 3.6; stereo 288 x 384, L = 8: 21.5 -> 9.3. Of the time
+// of these launches the vector unit is busy 74 % (256 x 256, L = 20), 59 % (353 x 517), 82 %
+// (1531 x 2039) and 64 % (stereo); on the smallest problems it is the serial chain of one
+// iteration (ROF 64 x 64: 24 %), of which 1.1 us is the round trip of the rim, measured with no
+// work around it.
+//
+// A cooperative launch goes through a queue of its own: the first of a process takes 10 ms more,
+// and launches of several streams run one after another. With many small problems on many
+// streams that can be slower than single launches side by side (64 x 64, L = 20, us per
+// iteration and problem: one stream 15.3 -> 6.2, eight streams 4.3 -> 6.0); a batch is the
+// better way then. Plain launches would not do: two that each held part of the chip would wait
+// for each other's blocks.
 //
 // 16 wavefronts a block leave 128 registers a lane. Whatever is not needed at once is kept out
 // of them: planes go in and out one element after another, rim words are waited for four labels
@@ -110,7 +119,7 @@ __device__ __forceinline__ float uniform(float x) {
 // which never changes, so a block lists its quadratic and its straddling (label, pixel) pairs
 // once, and its wavefronts walk the lists 64 pairs at a time. Walked label by label instead,
 // nearly every wavefront has some lane in every class and pays for all three (353 x 517, L =
-// 10: 29.5 us per iteration label by label, 16.5 with the lists). y of a listed point waits in
+// 10: 29.5 us per iteration label by label, 16 with the lists). y of a listed point waits in
 // its sbar's place, w in the slot of its place among the pixel's listed labels.
 //
 // RP > 1 (few labels, large images): a thread has its column's pixels in RP rows one below the
@@ -848,12 +857,13 @@ __global__ __launch_bounds__(1024) void pdhg_resident_kernel(ResidentArgs R) {
 }
 
 // What is built: chunks of up to 8 labels per thread, with a wavefront per label group in blocks
-// of up to 4 groups, and of 9 in blocks of one; the chunks of two or four label groups that a thread takes
-// together when the image has too many tiles for a wavefront per group; for long chunks (whose
-// LDS is scarce) blocks of one group of threads apart from those of several; several rows per
-// thread for few labels. Not built, because one launch per iteration is as fast: two rows of 6
-// quadratic labels (1501x192: 19.6 us on chip, 19.1 off it) and two groups of 5 quadratic labels
-// with additive values (701x256: 21.8 and 21.7, with bf16 duals 22.4 and 20.7). Returns the kernel for `phys` groups of threads and its PH.
+// of up to 4 groups, and of 9 in blocks of one; the chunks of two or four label groups that a
+// thread takes together when the image has too many tiles for a wavefront per group; for long
+// chunks (whose LDS is scarce) blocks of one group of threads apart from those of several; several
+// rows per thread for few labels. Not built, because one launch per iteration is as fast: two rows
+// of 6 quadratic labels (1501x192: 19.6 us on chip, 19.1 off it) and two groups of 5 quadratic
+// labels with additive values (701x256: 21.8 and 21.7, with bf16 duals 22.4 and 20.7). Returns the
+// kernel for `phys` groups of threads and its PH.
 template <int PIECE, bool ADD>
 inline const void *kernel_of(int ch, int lg, int rp, int phys, int *ph, bool keep) {
   if (keep) {   // the shapes of the images that are differentiated through

@@ -1,6 +1,7 @@
 // temporal.hip -- several iterations of the lifted primal-dual method (Sec. 4) per launch: two
 // per pass over HBM (this file's kernel, k <= 3), and as many as asked for with the state on
-// chip (resident.hpp; its plans and launches at the end of this file).
+// chip (the kernel of resident.hpp, whose instances, plans and launches are at the end of this
+// file).
 //
 // Two per pass, for problems with at most three label intervals (k <= 3).
 //
